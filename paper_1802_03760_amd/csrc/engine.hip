@@ -539,7 +539,9 @@ void run_static(gj_ctx* c, const gj_graph* g, const gj_query* q, int mode, uint6
                 P.bind[3].size() == 2 &&
                 ((is_bind(P.bind[3][0], 2, 0) && is_bind(P.bind[3][1], 0, 1)) ||
                  (is_bind(P.bind[3][1], 2, 0) && is_bind(P.bind[3][0], 0, 1)));
-  if ((shape == 1 && !P.has_ineq()) || cycle4) {  // diamond / 4-cycle: 2-path counts per a0
+  // diamond / 4-cycle: 2-path counts per pair (their index arithmetic takes
+  // fewer than 2^31 edges)
+  if (((shape == 1 && !P.has_ineq()) || cycle4) && v.m < (1ull << 31)) {
     KernelTimer timer(c);
     uint64_t o[3];
     if (cycle4)
