@@ -494,8 +494,28 @@ void run_static(gj_ctx* c, const gj_graph* g, const gj_query* q, int mode, uint6
     else if (out_of(2, 0b001) && out_of(3, 0b110)) shape = 1;  // a2: a0; a3: a1, a2
   }
   // transitive 5-clique: every atom out of an earlier attribute
-  if (!collect && c->strategy != 1 && P.m == 5 && P.filters.empty() && !P.ntri && P.seed_fwd && lo == 0 &&
-      hi == v.m && out_of(2, 0b0011) && out_of(3, 0b0111) && out_of(4, 0b1111)) {
+  const bool clique5 = !collect && c->strategy != 1 && P.m == 5 && P.filters.empty() && !P.ntri && P.seed_fwd &&
+                       lo == 0 && hi == v.m && out_of(2, 0b0011) && out_of(3, 0b0111) && out_of(4, 0b1111);
+  // both cliques on bit matrices of their greatest vertex by degree rank
+  if ((shape == 0 || clique5) && !P.has_ineq() && v.m < (1ull << 31) && !v.pmap[0] && !v.pmap[1]) {
+    KernelTimer timer(c);
+    uint64_t o[6];
+    if (clique_bits_count(c, v, g->n, g->old_of_new != nullptr, P.m, timer, o)) {
+      gj_stats s{};
+      s.prefixes[2] = v.m;
+      s.extensions[2] = o[1];
+      s.prefixes[3] = o[2];
+      s.extensions[3] = o[3];
+      s.prefixes[4] = clique5 ? o[4] : o[0];
+      s.extensions[4] = clique5 ? o[5] : 0;
+      s.matches = s.prefixes[P.m] = o[0];
+      s.kernel_ms = timer.total_ms();
+      s.kernel_launches = timer.launches();
+      *st = s;
+      return;
+    }
+  }
+  if (clique5) {
     KernelTimer timer(c);
     uint64_t o[7];
     uint32_t *x0 = nullptr, *x1 = nullptr;
@@ -545,9 +565,9 @@ void run_static(gj_ctx* c, const gj_graph* g, const gj_query* q, int mode, uint6
     KernelTimer timer(c);
     uint64_t o[3];
     if (cycle4)
-      cycle4_2p_count(c, v, g->n, timer, o);
+      cycle4_2p_count(c, v, g->n, g->old_of_new != nullptr, timer, o);
     else
-      diamond2p_count(c, v, g->n, timer, o);
+      diamond2p_count(c, v, g->n, g->old_of_new != nullptr, timer, o);
     gj_stats s{};
     s.prefixes[2] = v.m;
     s.extensions[2] = s.prefixes[3] = o[1];

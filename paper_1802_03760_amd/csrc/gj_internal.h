@@ -438,9 +438,17 @@ void launch_emit_values(gj_ctx* c, const uint32_t* F, uint64_t stride, uint64_t 
 void edge4_count(gj_ctx* c, const Version& v, int shape, const uint32_t above[4], const uint32_t below[4],
                  const uint64_t* hd, const uint32_t* hs, KernelTimer& timer, uint64_t out[5], uint32_t*& x0,
                  uint32_t*& x1, uint64_t& n_left);
-// clique.hip: the diamond over every forward edge of v by 2-path counts (no
+// cliquebits.hip: the transitive 4-clique or 5-clique (q = 4, 5; no
+// inequalities) over every forward edge of v: out = {matches, extensions[2],
+// prefixes[3], extensions[3], prefixes[4], extensions[4]} (the last two of the
+// 5-clique).  by_degree (here and below): ids ascend by degree.  False, and nothing counted, where some vertex has too many
+// neighbours of higher degree.
+bool clique_bits_count(gj_ctx* c, const Version& v, uint32_t n, bool by_degree, int q, KernelTimer& timer,
+                       uint64_t out[6]);
+// twopath.hip: the diamond over every forward edge of v by 2-path counts (no
 // inequalities): out = {matches, prefixes[3] = extensions[2], extensions[3]}.
-void diamond2p_count(gj_ctx* c, const Version& v, uint32_t n, KernelTimer& timer, uint64_t out[3]);
+void diamond2p_count(gj_ctx* c, const Version& v, uint32_t n, bool by_degree, KernelTimer& timer,
+                     uint64_t out[3]);
 // the transitive 5-clique by seed edge (forward CSR): out = matches,
 // prefixes[2], extensions[2], prefixes[3], extensions[3], prefixes[4],
 // extensions[4] of the seeds it took; the others (x0, x1: n_left pairs, in
@@ -448,10 +456,11 @@ void diamond2p_count(gj_ctx* c, const Version& v, uint32_t n, KernelTimer& timer
 void clique5_count(gj_ctx* c, const Version& v, const uint32_t above[5], const uint32_t below[5],
                    const uint64_t* hd, const uint32_t* hs, KernelTimer& timer, uint64_t out[7], uint32_t*& x0,
                    uint32_t*& x1, uint64_t& n_left);
-// clique.hip: the 4-cycle a0 -> a1 -> a2 -> a3 -> a0 by forward and backward
+// twopath.hip: the 4-cycle a0 -> a1 -> a2 -> a3 -> a0 by forward and backward
 // 2-path counts (no inequalities): out = {matches, prefixes[3] =
 // extensions[2], extensions[3]}.
-void cycle4_2p_count(gj_ctx* c, const Version& v, uint32_t n, KernelTimer& timer, uint64_t out[3]);
+void cycle4_2p_count(gj_ctx* c, const Version& v, uint32_t n, bool by_degree, KernelTimer& timer,
+                     uint64_t out[3]);
 // tri.hip: the triangle relation of the graph's current version (replaces
 // g->tri); frees it
 void tri_index_build(gj_ctx* c, gj_graph* g);

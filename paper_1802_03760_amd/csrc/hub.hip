@@ -1,0 +1,199 @@
+// The renaming by descending degree (hub.h).
+#include <algorithm>
+
+#include "gj_internal.h"
+#include "hub.h"
+#include "prim.h"
+
+namespace gj {
+
+__global__ void k_hub_keys(const uint32_t* __restrict__ rp0, const uint32_t* __restrict__ rp1, uint32_t n,
+                           uint32_t top, uint64_t* __restrict__ keys) {
+  const uint64_t gs = (uint64_t)gridDim.x * blockDim.x;
+  for (uint64_t v = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n; v += gs) {
+    const uint32_t d = (rp0[v + 1] - rp0[v]) + (rp1[v + 1] - rp1[v]);  // at most top
+    keys[v] = ((uint64_t)(top - d) << 32) | v;
+  }
+}
+
+// new id = position in descending degree order; degrees in the new order
+__global__ void k_hub_ids(const uint64_t* __restrict__ keys, const uint32_t* __restrict__ rp0,
+                          const uint32_t* __restrict__ rp1, uint32_t n, uint32_t* __restrict__ new_of_old,
+                          uint32_t* __restrict__ d0, uint32_t* __restrict__ d1) {
+  const uint64_t gs = (uint64_t)gridDim.x * blockDim.x;
+  for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gs) {
+    const uint32_t o = (uint32_t)keys[i];
+    new_of_old[o] = (uint32_t)i;
+    d0[i] = rp0[o + 1] - rp0[o];
+    d1[i] = rp1[o + 1] - rp1[o];
+  }
+}
+
+__global__ void k_hub_edges(const uint32_t* __restrict__ row, const uint32_t* __restrict__ col, uint64_t m,
+                            const uint32_t* __restrict__ new_of_old, uint64_t* __restrict__ keys) {
+  const uint64_t gs = (uint64_t)gridDim.x * blockDim.x;
+  for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < m; i += gs)
+    keys[i] = ((uint64_t)new_of_old[row[i]] << 32) | new_of_old[col[i]];
+}
+
+// rows and columns of the sorted keys, and the swapped keys for the other
+// direction (null: none)
+__global__ void k_hub_split(const uint64_t* __restrict__ keys, uint64_t m, uint32_t* __restrict__ row,
+                            uint32_t* __restrict__ col, uint64_t* __restrict__ swapped) {
+  const uint64_t gs = (uint64_t)gridDim.x * blockDim.x;
+  for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < m; i += gs) {
+    const uint64_t k = keys[i];
+    row[i] = (uint32_t)(k >> 32);
+    col[i] = (uint32_t)k;
+    if (swapped) swapped[i] = (k << 32) | (k >> 32);
+  }
+}
+
+// The same graph with id v renamed to n - 1 - v: every array backwards.
+__global__ void k_hub_reverse(const uint32_t* __restrict__ rp, const uint32_t* __restrict__ row,
+                              const uint32_t* __restrict__ col, uint64_t m, uint32_t n, uint32_t* __restrict__ orp,
+                              uint32_t* __restrict__ orow, uint32_t* __restrict__ ocol) {
+  const uint64_t gs = (uint64_t)gridDim.x * blockDim.x, t = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  for (uint64_t i = t; i < m; i += gs) {
+    orow[m - 1 - i] = n - 1 - row[i];
+    ocol[m - 1 - i] = n - 1 - col[i];
+  }
+  for (uint64_t v = t; v <= n; v += gs) orp[v] = (uint32_t)m - rp[n - v];
+}
+
+// end of every row's prefix, and its quads; both directions
+__global__ void k_hub_prefix(HubGraph g, uint32_t* __restrict__ end, uint32_t* __restrict__ quads) {
+  const uint64_t gs = (uint64_t)gridDim.x * blockDim.x;
+  for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < 2ull * g.n; i += gs) {
+    const int s = i >= g.n;
+    const uint32_t u = (uint32_t)(s ? i - g.n : i);
+    const uint32_t b = g.rp[s][u], e = lower_bound_u32(g.col[s], b, g.rp[s][(uint64_t)u + 1], u);
+    end[i] = e;
+    quads[i] = (e - b + 3) / 4;
+  }
+}
+
+// The prefixes' entries into their quads, the last one of a prefix padding its
+// quad; both directions.
+__global__ void k_hub_quads(HubGraph g, const uint32_t* __restrict__ row0, const uint32_t* __restrict__ row1,
+                            uint64_t m, uint32_t* __restrict__ pre) {
+  const uint64_t gs = (uint64_t)gridDim.x * blockDim.x;
+  for (int s = 0; s < 2; ++s)
+    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < m; i += gs) {
+      const uint32_t x = (s ? row1 : row0)[i], y = g.col[s][i];
+      if (y >= x) continue;
+      uint64_t at = (uint64_t)g.pq[s][x] * 4 + (i - g.rp[s][x]);
+      pre[at] = y;
+      if (i + 1 == g.end[s][x])
+        while (++at & 3) pre[at] = ~0u;
+    }
+}
+
+// first quad with an id of kTpHubs or above; both directions
+__global__ void k_hub_above(HubGraph g, uint32_t* __restrict__ mq) {
+  const uint64_t gs = (uint64_t)gridDim.x * blockDim.x;
+  for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < 2ull * g.n; i += gs) {
+    const uint64_t u = i >= g.n ? i - g.n : i;
+    uint32_t lo = g.pq[0][i], len = g.pq[0][i + 1] - lo;  // the directions' arrays follow each other
+    if (u <= kTpHubs) {
+      lo += len;
+    } else {
+      const uint32_t e = lo + len;
+      while (len > 0) {
+        const uint32_t half = len >> 1;
+        if (g.pre[(uint64_t)lo + half].w < kTpHubs) {
+          lo += half + 1;
+          len -= half + 1;
+        } else {
+          len = half;
+        }
+      }
+      if (lo < e) {  // the last quad may hold padding only beyond its ids below
+        const uint4 t = g.pre[lo];
+        const auto above = [](uint32_t x) { return x >= kTpHubs && x != ~0u; };
+        if (!(above(t.x) || above(t.y) || above(t.z) || above(t.w))) lo = e;
+      }
+    }
+    mq[i] = lo;
+  }
+}
+
+void hub_above(gj_ctx* c, HubGraph& g) {
+  uint32_t* mq = (uint32_t*)ws_get(c, "tp_mq", 2 * (uint64_t)g.n * sizeof(uint32_t));
+  k_hub_above<<<grid_for(2ull * g.n, kBlock, 1u << 14), kBlock, 0, c->stream>>>(g, mq);
+  GJ_HIP(hipGetLastError());
+  g.mq[0] = mq;
+  g.mq[1] = mq + g.n;
+}
+
+HubGraph hub_graph(gj_ctx* c, const Version& v, uint32_t n, HubOrder order, const uint32_t*& row) {
+  const uint64_t m = v.m;
+  HubGraph g{};
+  g.n = n;
+  const unsigned gn = grid_for(n, kBlock, 1u << 14), ge = grid_for(m, kBlock * 4, 1u << 14);
+  auto words = [&](const std::string& name, uint64_t count) {
+    return (uint32_t*)ws_get(c, "tp_" + name, count * sizeof(uint32_t));
+  };
+  const uint32_t* rows[2];
+  if (order == HubOrder::kAsIs) {
+    for (int s = 0; s < 2; ++s) {
+      g.rp[s] = v.d[s].rp;
+      g.col[s] = v.d[s].col;
+      rows[s] = v.d[s].row;
+    }
+  } else {
+    uint32_t *rp[2], *orow[2], *ocol[2];
+    for (int s = 0; s < 2; ++s) {
+      const std::string z = s ? "1" : "0";
+      g.rp[s] = rp[s] = words("rp" + z, (uint64_t)n + 1);
+      g.col[s] = ocol[s] = words("col" + z, m + 1);
+      rows[s] = orow[s] = words("row" + z, m + 1);
+    }
+    if (order == HubOrder::kReversed) {
+      for (int s = 0; s < 2; ++s)
+        k_hub_reverse<<<ge, kBlock, 0, c->stream>>>(v.d[s].rp, v.d[s].row, v.d[s].col, m, n, rp[s], orow[s], ocol[s]);
+    } else {
+      uint64_t* vk = (uint64_t*)ws_get(c, "tp_vk", (uint64_t)n * sizeof(uint64_t));
+      uint64_t* vk2 = (uint64_t*)ws_get(c, "tp_vk2", (uint64_t)n * sizeof(uint64_t));
+      uint64_t* keys = (uint64_t*)ws_get(c, "tp_keys", (m + 1) * sizeof(uint64_t));
+      uint64_t* alt = (uint64_t*)ws_get(c, "tp_alt", (m + 1) * sizeof(uint64_t));
+      uint32_t* ids = words("ids", n);
+      uint32_t* deg = words("deg", 2 * (uint64_t)n);
+      const uint32_t top = v.max_deg[0] + v.max_deg[1];
+      k_hub_keys<<<gn, kBlock, 0, c->stream>>>(v.d[0].rp, v.d[1].rp, n, top, vk);
+      const uint64_t* vs = sort_u64(c, vk, vk2, n, 0, bits_for(top + 1));  // stable: equal degrees by id
+      k_hub_ids<<<gn, kBlock, 0, c->stream>>>(vs, v.d[0].rp, v.d[1].rp, n, ids, deg, deg + n);
+      k_hub_edges<<<ge, kBlock, 0, c->stream>>>(v.d[0].row, v.d[0].col, m, ids, keys);
+      const int bits = bits_for(n);
+      for (int s = 0; s < 2; ++s) {
+        scan_u32(c, deg + (uint64_t)s * n, rp[s], n);
+        // the reverse keys come out of the forward order, already ascending in
+        // their low half: a stable sort by the high half finishes them
+        uint64_t* sorted = sort_u64(c, keys, alt, m, s ? 0 : bits, bits);
+        uint64_t* other = sorted == keys ? alt : keys;
+        k_hub_split<<<ge, kBlock, 0, c->stream>>>(sorted, m, orow[s], ocol[s], s ? nullptr : other);
+        keys = other;
+        alt = sorted;
+      }
+    }
+  }
+  // every edge is in one prefix, of at most 2 min(n, m) that are not empty
+  const uint64_t quads = (m + 6 * std::min<uint64_t>(n, m)) / 4 + 2;
+  uint4* pre = (uint4*)ws_get(c, "tp_pre", quads * sizeof(uint4));
+  uint32_t* qn = words("qn", 2 * (uint64_t)n);
+  uint32_t* end = words("end", 2 * (uint64_t)n);
+  uint32_t* pq = words("pq", 2 * (uint64_t)n + 1);
+  g.pre = pre;
+  k_hub_prefix<<<grid_for(2ull * n, kBlock, 1u << 14), kBlock, 0, c->stream>>>(g, end, qn);
+  scan_u32(c, qn, pq, 2 * (uint64_t)n);
+  for (int s = 0; s < 2; ++s) {
+    g.end[s] = end + (uint64_t)s * n;
+    g.pq[s] = pq + (uint64_t)s * n;
+  }
+  k_hub_quads<<<ge, kBlock, 0, c->stream>>>(g, rows[0], rows[1], m, (uint32_t*)pre);
+  GJ_HIP(hipGetLastError());
+  row = rows[0];
+  return g;
+}
+
+}  // namespace gj

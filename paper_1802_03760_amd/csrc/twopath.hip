@@ -35,138 +35,13 @@
 #include <algorithm>
 
 #include "gj_internal.h"
+#include "hub.h"
 #include "prim.h"
 
 namespace gj {
 
-// The renamed graph: per direction (0 out-, 1 in-neighbours) rows sorted by
-// new id, row u at col[rp[u] .. rp[u + 1]); end[u] closes the prefix of ids below u.  The prefixes are stored again on
-// their own, in quads of four entries padded with ~0: direction s's of u at
-// quads (s ? pq[0][n] : 0) + [pq[s][u], pq[s][u + 1]) of pre, so that a walk
-// loads 16 aligned bytes a lane and an entry's value alone says whether it
-// counts.  mq[s][u]: the first of those quads with an id of kTpHubs or above.
-struct HubGraph {
-  const uint32_t* rp[2];
-  const uint32_t* end[2];
-  const uint32_t* pq[2];
-  const uint32_t* mq[2];
-  const uint32_t* col[2];
-  const uint4* pre;
-  uint32_t n;
-  __device__ __forceinline__ uint32_t deg(int s, uint64_t v) const { return rp[s][v + 1] - rp[s][v]; }
-  __device__ __forceinline__ const uint32_t* row(int s, uint64_t v) const { return col[s] + rp[s][v]; }
-};
-
-constexpr uint32_t kTpHubs = 16384;  // ids below it: 8-bit counter pairs for all of them take 32 KiB
-
 // Accumulators of one call.
 enum { kTpAB, kTpOI, kTpRec2, kTpBoth, kTpMid, kTpRecUp2, kTpPaths, kTpMin, kTpAcc };
-
-// ---------------------------------------------------------------- renaming
-__global__ void k_hub_keys(const uint32_t* __restrict__ rp0, const uint32_t* __restrict__ rp1, uint32_t n,
-                           uint32_t top, uint64_t* __restrict__ keys) {
-  const uint64_t gs = (uint64_t)gridDim.x * blockDim.x;
-  for (uint64_t v = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n; v += gs) {
-    const uint32_t d = (rp0[v + 1] - rp0[v]) + (rp1[v + 1] - rp1[v]);  // at most top
-    keys[v] = ((uint64_t)(top - d) << 32) | v;
-  }
-}
-
-// new id = position in descending degree order; degrees in the new order
-__global__ void k_hub_ids(const uint64_t* __restrict__ keys, const uint32_t* __restrict__ rp0,
-                          const uint32_t* __restrict__ rp1, uint32_t n, uint32_t* __restrict__ new_of_old,
-                          uint32_t* __restrict__ d0, uint32_t* __restrict__ d1) {
-  const uint64_t gs = (uint64_t)gridDim.x * blockDim.x;
-  for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gs) {
-    const uint32_t o = (uint32_t)keys[i];
-    new_of_old[o] = (uint32_t)i;
-    d0[i] = rp0[o + 1] - rp0[o];
-    d1[i] = rp1[o + 1] - rp1[o];
-  }
-}
-
-__global__ void k_hub_edges(const uint32_t* __restrict__ row, const uint32_t* __restrict__ col, uint64_t m,
-                            const uint32_t* __restrict__ new_of_old, uint64_t* __restrict__ keys) {
-  const uint64_t gs = (uint64_t)gridDim.x * blockDim.x;
-  for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < m; i += gs)
-    keys[i] = ((uint64_t)new_of_old[row[i]] << 32) | new_of_old[col[i]];
-}
-
-// end of every row's prefix, and its quads
-__global__ void k_hub_prefix(const uint32_t* __restrict__ rp, const uint64_t* __restrict__ keys, uint32_t n,
-                             uint32_t* __restrict__ end, uint32_t* __restrict__ quads) {
-  const uint64_t gs = (uint64_t)gridDim.x * blockDim.x;
-  for (uint64_t u = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; u < n; u += gs) {
-    const uint32_t b = rp[u];
-    uint32_t lo = b, len = rp[u + 1] - b;
-    while (len > 0) {
-      const uint32_t half = len >> 1;
-      if ((uint32_t)keys[(uint64_t)lo + half] < (uint32_t)u) {
-        lo += half + 1;
-        len -= half + 1;
-      } else {
-        len = half;
-      }
-    }
-    end[u] = lo;
-    quads[u] = (lo - b + 3) / 4;
-  }
-}
-
-// Columns of the sorted keys and, for the forward direction, the rows and the
-// swapped keys; the prefixes' entries into their quads, the last one of a
-// prefix padding its quad.
-__global__ void k_hub_cols(const uint64_t* __restrict__ keys, uint64_t m, const uint32_t* __restrict__ rp,
-                           const uint32_t* __restrict__ end, const uint32_t* __restrict__ pq,
-                           const uint32_t* __restrict__ before, uint32_t* __restrict__ col,
-                           uint32_t* __restrict__ row, uint64_t* __restrict__ swapped, uint32_t* __restrict__ pre) {
-  const uint64_t gs = (uint64_t)gridDim.x * blockDim.x;
-  const uint64_t base = before ? *before : 0;
-  for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < m; i += gs) {
-    const uint64_t k = keys[i];
-    const uint32_t x = (uint32_t)(k >> 32), y = (uint32_t)k;
-    col[i] = y;
-    if (row) {
-      row[i] = x;
-      swapped[i] = (k << 32) | x;
-    }
-    if (y < x) {
-      uint64_t at = (base + pq[x]) * 4 + (i - rp[x]);
-      pre[at] = y;
-      if (i + 1 == end[x])
-        while (++at & 3) pre[at] = ~0u;
-    }
-  }
-}
-
-__global__ void k_hub_above(const uint32_t* __restrict__ pq, const uint32_t* __restrict__ before, uint32_t n,
-                            const uint4* __restrict__ pre, uint32_t* __restrict__ mq) {
-  const uint64_t gs = (uint64_t)gridDim.x * blockDim.x;
-  const uint4* q = pre + (before ? *before : 0);
-  for (uint64_t u = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; u < n; u += gs) {
-    uint32_t lo = pq[u], len = pq[u + 1] - lo;
-    if (u <= kTpHubs) {
-      lo += len;
-    } else {
-      const uint32_t e = lo + len;
-      while (len > 0) {
-        const uint32_t half = len >> 1;
-        if (q[(uint64_t)lo + half].w < kTpHubs) {
-          lo += half + 1;
-          len -= half + 1;
-        } else {
-          len = half;
-        }
-      }
-      if (lo < e) {  // the last quad may hold padding only beyond its ids below
-        const uint4 t = q[lo];
-        const auto above = [](uint32_t x) { return x >= kTpHubs && x != ~0u; };
-        if (!(above(t.x) || above(t.y) || above(t.z) || above(t.w))) lo = e;
-      }
-    }
-    mq[u] = lo;
-  }
-}
 
 // ---------------------------------------------------------------- reciprocal pairs
 // Per vertex, its reciprocal neighbours (rec) and those below it (rec_lo):
@@ -329,10 +204,6 @@ __global__ void __launch_bounds__(kBlock) k_hub_classes(HubGraph g, int cycle, u
 }
 
 // ---------------------------------------------------------------- the walk
-__device__ __forceinline__ uint32_t lane_value(uint32_t v, int lane) {
-  return (uint32_t)__builtin_amdgcn_readlane((int)v, lane);
-}
-
 // w's neighbours: the first nin of the walk's rows belong to in-neighbours
 // (fields A, O), the other nout to out-neighbours (B, I).
 struct HubRow {
@@ -380,13 +251,12 @@ __device__ __forceinline__ void batch_bounds(const HubGraph& g, int pass, int fr
 }
 
 // Leaves out the quads below s0 and moves the rows that have any to the
-// lowest lanes.  base: where the in-prefixes start.
-__device__ __forceinline__ void batch_pack(const HubGraph& g, uint32_t base, int pass, uint32_t s0, HubBatch& t) {
+// lowest lanes.
+__device__ __forceinline__ void batch_pack(const HubGraph& g, uint32_t s0, HubBatch& t) {
   uint32_t n = 0;
   t.p = 0;
   if (t.live) {
-    const uint32_t at = t.out != (pass != 0) ? 0 : base;
-    uint32_t b = at + t.b, len = t.e - t.b;
+    uint32_t b = t.b, len = t.e - t.b;
     if (s0)
       while (len > 0) {
         const uint32_t half = len >> 1;
@@ -398,7 +268,7 @@ __device__ __forceinline__ void batch_pack(const HubGraph& g, uint32_t base, int
         }
       }
     t.p = b;
-    n = at + t.e - b;
+    n = t.e - b;
   }
   const uint64_t some = __ballot(n != 0);
   const uint32_t cn = (uint32_t)__popcll(some);
@@ -411,75 +281,9 @@ __device__ __forceinline__ void batch_pack(const HubGraph& g, uint32_t base, int
   t.live = (uint32_t)lane_id() < cn;
 }
 
-// Sixteen lanes to a row, a quad to a lane, so a wave walks four rows side by
-// side and a group that finishes one takes the batch's next; DEPTH loads are
-// in flight.  Calls add(x, side) for every entry and for fillers (~0), so that
-// it can do without a branch per entry.  A row ends at its first quad beyond
-// lim.  Issue-bound (about 60 instructions for 256 entries): addressing is
-// per lane, since a row to a wave kept the scalar unit busy with row
-// bookkeeping, and lengths are tested per quad, not per entry.
-template <int DEPTH, class F>
-__device__ __forceinline__ void walk_batch(const uint4* __restrict__ pre, const HubBatch& t, uint32_t lim, F add) {
-  const uint32_t lane = lane_id(), sub = lane & 15;
-  const uint64_t group = 0xFFFFull << (lane & 48), below = (1ull << (lane & 48)) - 1;
-  const uint32_t cn = (uint32_t)__popcll(__ballot(t.live));
-  if (!cn) return;
-  uint32_t next = 4, row = lane >> 4;  // the batch's rows taken; this group's
-  uint32_t p = 0, left = 0, side = 0;  // left: quads of the row from p on; 0 once the batch has no more
-  auto take = [&](bool mine) {  // all lanes
-    const uint32_t a = __shfl(t.p, row & 63, 64), l = __shfl(t.len, row & 63, 64);
-    if (mine) {
-      p = a + sub;
-      left = row < cn ? l & 0x7FFFFFFFu : 0;
-      side = l >> 31;
-    }
-  };
-  uint4 q[DEPTH];
-  uint32_t qside[DEPTH], qrow[DEPTH];
-  uint64_t qlive[DEPTH];
-  auto issue = [&](int d) {
-    q[d] = make_uint4(~0u, ~0u, ~0u, ~0u);
-    qlive[d] = __ballot(left != 0);
-    qside[d] = side;
-    qrow[d] = row;
-    if (sub < left) q[d] = pre[p];
-    // the group's next 64 entries, of the row or of another
-    const bool more = left > 16;
-    const uint64_t ask = qlive[d] & ~__ballot(more) & 0x0001000100010001ull;  // a bit per group
-    if (ask) {
-      const bool mine = left && !more;
-      if (mine) row = next + (uint32_t)__popcll(ask & below);
-      next += (uint32_t)__popcll(ask);
-      if (more) left -= 16;
-      p += 16;
-      take(mine);
-    } else {
-      left -= more ? 16 : 0;
-      p += 16;
-    }
-  };
-  take(true);
-#pragma unroll
-  for (int d = 0; d < DEPTH; ++d) issue(d);
-  for (;;) {
-#pragma unroll
-    for (int d = 0; d < DEPTH; ++d) {
-      if (!qlive[d]) return;  // issued in order: none behind it either
-      // the rest of a row whose quads reach lim lies beyond it: one more step ends it
-      const uint64_t stop = __ballot(q[d].w >= lim);
-      add(q[d].x, qside[d]);
-      add(q[d].y, qside[d]);
-      add(q[d].z, qside[d]);
-      add(q[d].w, qside[d]);
-      if ((stop & group) && row == qrow[d] && left > 1) left = 1;
-      issue(d);
-    }
-  }
-}
-
 // The walk of w's batches from its first, t (packed from s0).
 template <int DEPTH, class F>
-__device__ __forceinline__ void walk_pairs(const HubGraph& g, uint32_t base, int pass, int from, const HubRow& h, HubBatch t,
+__device__ __forceinline__ void walk_pairs(const HubGraph& g, int pass, int from, const HubRow& h, HubBatch t,
                                            uint32_t s0, uint32_t lim, uint32_t wave, uint32_t nwaves, F add) {
   const uint64_t d = (uint64_t)h.nin + h.nout;
   const uint32_t G = batch_size(h, nwaves);
@@ -493,8 +297,8 @@ __device__ __forceinline__ void walk_pairs(const HubGraph& g, uint32_t base, int
   for (; i0 < d; i0 += step) {
     HubBatch f{};
     if (i0 + 2 * step < d) f = batch_load(g, h, i0 + 2 * step, G);
-    walk_batch<DEPTH>(g.pre, t, lim, add);
-    if (i0 + step < d) batch_pack(g, base, pass, s0, n);
+    walk_batch<DEPTH, 31>(g.pre, t.p, t.len, (uint32_t)__popcll(__ballot(t.live)), lim, add);
+    if (i0 + step < d) batch_pack(g, s0, n);
     t = n;
     batch_bounds(g, pass, from, f);
     n = f;
@@ -515,7 +319,7 @@ struct HubFeed {
   const uint32_t* ws;
   uint64_t total, step, k;
   int pass;
-  uint32_t wave, base;
+  uint32_t wave;
   HubRow cur, n1, n2;
   uint32_t w3;
   HubBatch t, b1;
@@ -530,14 +334,14 @@ struct HubFeed {
   }
   __device__ __forceinline__ HubFeed(const HubGraph& g_, int pass_, const uint32_t* ws_, uint64_t total_,
                                      uint64_t step_, uint64_t k_, uint32_t wave_)
-      : g(g_), ws(ws_), total(total_), step(step_), k(k_), pass(pass_), wave(wave_), base(g_.pq[0][g_.n]) {
+      : g(g_), ws(ws_), total(total_), step(step_), k(k_), pass(pass_), wave(wave_) {
     cur = row(k, id(k));
     n1 = row(k + step, id(k + step));
     n2 = row(k + 2 * step, id(k + 2 * step));
     w3 = id(k + 3 * step);
     t = first(cur);
     batch_bounds(g, pass, 0, t);
-    batch_pack(g, base, pass, 0, t);
+    batch_pack(g, 0, t);
     b1 = first(n1);
   }
   __device__ __forceinline__ bool more() const { return k < total; }
@@ -549,7 +353,7 @@ struct HubFeed {
     HubBatch b2 = first(n2);
     batch_bounds(g, pass, 0, b1);
     walk();
-    batch_pack(g, base, pass, 0, b1);
+    batch_pack(g, 0, b1);
     t = b1;
     b1 = b2;
     cur = n1;
@@ -622,9 +426,9 @@ __global__ void __launch_bounds__(1024) k_hub_dense(HubGraph g, int pass, int op
         if (s0) {
           f.t = f.first(f.cur);
           batch_bounds(g, pass, 0, f.t);
-          batch_pack(g, f.base, pass, s0, f.t);
+          batch_pack(g, s0, f.t);
         }
-        walk_pairs<4>(g, f.base, pass, 0, f.cur, f.t, s0, lim, wave, kNW, [&](uint32_t x, uint32_t side) {
+        walk_pairs<4>(g, pass, 0, f.cur, f.t, s0, lim, wave, kNW, [&](uint32_t x, uint32_t side) {
           const bool in = x - s0 < lim - s0;  // else the lane's own idle word
           if (BITS == 16)
             atomicAdd(&cnt[in ? x - s0 : idle], 1u << (16 * side));
@@ -672,7 +476,7 @@ __global__ void __launch_bounds__(kBlock) k_hub_small(HubGraph g, int pass, int 
         a = f.first(f.cur);
         batch_bounds(g, pass, 1, a);
       }
-      walk_pairs<2>(g, f.base, pass, 0, f.cur, f.t, 0, lim, wave, kNW, [&](uint32_t x, uint32_t side) {
+      walk_pairs<2>(g, pass, 0, f.cur, f.t, 0, lim, wave, kNW, [&](uint32_t x, uint32_t side) {
         const uint32_t y = x < lim ? x : idle;
         atomicAdd(&cnt[y >> 1], (1u << (8 * side)) << (16 * (y & 1)));
       });
@@ -682,9 +486,9 @@ __global__ void __launch_bounds__(kBlock) k_hub_small(HubGraph g, int pass, int 
       });
       __syncthreads();
       if (ABOVE) {
-        batch_pack(g, f.base, pass, 0, a);
+        batch_pack(g, 0, a);
         const uint32_t w = f.cur.w;
-        walk_pairs<2>(g, f.base, pass, 1, f.cur, a, 0, w, wave, kNW, [&](uint32_t x, uint32_t side) {
+        walk_pairs<2>(g, pass, 1, f.cur, a, 0, w, wave, kNW, [&](uint32_t x, uint32_t side) {
           if (x >= kTpHubs && x < w) hash_add<kSlots>(cnt, cnt + kSlots, x, side);
         });
         __syncthreads();
@@ -722,7 +526,7 @@ __global__ void __launch_bounds__(kBlock) k_hub_wave(HubGraph g, int pass, int o
   while (f.more())
     f.next([&] {
       const uint32_t w = f.cur.w;
-      walk_pairs<2>(g, f.base, pass, 0, f.cur, f.t, 0, w, 0, 1, [&](uint32_t x, uint32_t side) {
+      walk_pairs<2>(g, pass, 0, f.cur, f.t, 0, w, 0, 1, [&](uint32_t x, uint32_t side) {
         if (x < w) hash_add<kSlots>(key, cnt, x, side);
       });
       sync();
@@ -932,62 +736,8 @@ __global__ void __launch_bounds__(kTpDirectNT) k_tp_direct(HubGraph g, uint32_t*
 }
 
 // ---------------------------------------------------------------- host
-static HubGraph hub_graph(gj_ctx* c, const Version& v, uint32_t n, const uint32_t*& row) {
-  const uint64_t m = v.m;
-  uint64_t* vk = (uint64_t*)ws_get(c, "tp_vk", (uint64_t)n * sizeof(uint64_t));
-  uint64_t* vk2 = (uint64_t*)ws_get(c, "tp_vk2", (uint64_t)n * sizeof(uint64_t));
-  uint32_t* ids = (uint32_t*)ws_get(c, "tp_ids", (uint64_t)n * sizeof(uint32_t));
-  uint32_t* deg = (uint32_t*)ws_get(c, "tp_deg", 2 * (uint64_t)n * sizeof(uint32_t));
-  uint64_t* keys = (uint64_t*)ws_get(c, "tp_keys", (m + 1) * sizeof(uint64_t));
-  uint64_t* alt = (uint64_t*)ws_get(c, "tp_alt", (m + 1) * sizeof(uint64_t));
-  uint32_t* rows = (uint32_t*)ws_get(c, "tp_row", (m + 1) * sizeof(uint32_t));
-  // every edge is in one prefix, of at most 2 min(n, m) that are not empty
-  const uint64_t quads = (m + 6 * std::min<uint64_t>(n, m)) / 4 + 2;
-  uint4* pre = (uint4*)ws_get(c, "tp_pre", quads * sizeof(uint4));
-  uint32_t* qn = (uint32_t*)ws_get(c, "tp_qn", (uint64_t)n * sizeof(uint32_t));
-  HubGraph g{};
-  g.n = n;
-  g.pre = pre;
-  const unsigned gn = grid_for(n, kBlock, 1u << 14), ge = grid_for(m, kBlock * 4, 1u << 14);
-  const uint32_t top = v.max_deg[0] + v.max_deg[1];
-  k_hub_keys<<<gn, kBlock, 0, c->stream>>>(v.d[0].rp, v.d[1].rp, n, top, vk);
-  const uint64_t* vs = sort_u64(c, vk, vk2, n, 0, bits_for(top + 1));  // stable: equal degrees by id
-  k_hub_ids<<<gn, kBlock, 0, c->stream>>>(vs, v.d[0].rp, v.d[1].rp, n, ids, deg, deg + n);
-  k_hub_edges<<<ge, kBlock, 0, c->stream>>>(v.d[0].row, v.d[0].col, m, ids, keys);
-  GJ_HIP(hipGetLastError());
-  const int bits = bits_for(n);
-  for (int s = 0; s < 2; ++s) {
-    const std::string z = s ? "1" : "0";
-    uint32_t* rp = (uint32_t*)ws_get(c, "tp_rp" + z, ((uint64_t)n + 1) * sizeof(uint32_t));
-    uint32_t* end = (uint32_t*)ws_get(c, "tp_end" + z, (uint64_t)n * sizeof(uint32_t));
-    uint32_t* pq = (uint32_t*)ws_get(c, "tp_pq" + z, ((uint64_t)n + 1) * sizeof(uint32_t));
-    uint32_t* col = (uint32_t*)ws_get(c, "tp_col" + z, (m + 1) * sizeof(uint32_t));
-    uint32_t* mq = (uint32_t*)ws_get(c, "tp_mq" + z, (uint64_t)n * sizeof(uint32_t));
-    scan_u32(c, deg + (uint64_t)s * n, rp, n);
-    // the reverse keys come out of the forward order, already ascending in
-    // their low half: a stable sort by the high half finishes them
-    uint64_t* sorted = sort_u64(c, keys, alt, m, s ? 0 : bits, bits);
-    uint64_t* other = sorted == keys ? alt : keys;
-    k_hub_prefix<<<gn, kBlock, 0, c->stream>>>(rp, sorted, n, end, qn);
-    scan_u32(c, qn, pq, n);
-    const uint32_t* before = s ? g.pq[0] + n : nullptr;
-    k_hub_cols<<<ge, kBlock, 0, c->stream>>>(sorted, m, rp, end, pq, before, col, s ? nullptr : rows,
-                                             s ? nullptr : other, (uint32_t*)pre);
-    k_hub_above<<<gn, kBlock, 0, c->stream>>>(pq, before, n, pre, mq);
-    GJ_HIP(hipGetLastError());
-    keys = other;
-    alt = sorted;
-    g.rp[s] = rp;
-    g.col[s] = col;
-    g.end[s] = end;
-    g.pq[s] = pq;
-    g.mq[s] = mq;
-  }
-  row = rows;
-  return g;
-}
-
-static void count_2path(gj_ctx* c, const Version& v, uint32_t n, bool cycle, KernelTimer& timer, uint64_t out[3]) {
+static void count_2path(gj_ctx* c, const Version& v, uint32_t n, bool by_degree, bool cycle, KernelTimer& timer,
+                        uint64_t out[3]) {
   for (int i = 0; i < 3; ++i) out[i] = 0;
   if (!v.m) return;
   // control words: the accumulators, the lists' lengths per pass and class,
@@ -1023,7 +773,8 @@ static void count_2path(gj_ctx* c, const Version& v, uint32_t n, bool cycle, Ker
     return;
   }
   const uint32_t* row = nullptr;
-  const HubGraph g = hub_graph(c, v, n, row);
+  HubGraph g = hub_graph(c, v, n, by_degree ? HubOrder::kReversed : HubOrder::kDegree, row);
+  hub_above(c, g);
   uint32_t* lists = (uint32_t*)ws_get(c, "tp_lists", (uint64_t)kLists * n * sizeof(uint32_t));
   uint32_t* rec = (uint32_t*)ws_get(c, "tp_rec", 2 * (uint64_t)n * sizeof(uint32_t));
   GJ_HIP(hipMemsetAsync(rec, 0, 2 * (uint64_t)n * sizeof(uint32_t), c->stream));
@@ -1058,12 +809,14 @@ static void count_2path(gj_ctx* c, const Version& v, uint32_t n, bool cycle, Ker
   out[2] = h[kTpMin];
 }
 
-void diamond2p_count(gj_ctx* c, const Version& v, uint32_t n, KernelTimer& timer, uint64_t out[3]) {
-  count_2path(c, v, n, false, timer, out);
+void diamond2p_count(gj_ctx* c, const Version& v, uint32_t n, bool by_degree, KernelTimer& timer,
+                     uint64_t out[3]) {
+  count_2path(c, v, n, by_degree, false, timer, out);
 }
 
-void cycle4_2p_count(gj_ctx* c, const Version& v, uint32_t n, KernelTimer& timer, uint64_t out[3]) {
-  count_2path(c, v, n, true, timer, out);
+void cycle4_2p_count(gj_ctx* c, const Version& v, uint32_t n, bool by_degree, KernelTimer& timer,
+                     uint64_t out[3]) {
+  count_2path(c, v, n, by_degree, true, timer, out);
 }
 
 }  // namespace gj

@@ -1,0 +1,56 @@
+"""Whole transitive 4-clique and 5-clique counts (counts and every counter)
+against the oracle, on graphs that put a vertex at the edges of the bit-matrix
+kernels' size classes, and beyond the largest (left to the edge-grouped
+kernels)."""
+import numpy as np
+import pytest
+
+import oracle
+import synth
+from tests import queries as Q
+
+pytestmark = pytest.mark.gpu
+
+
+def check(n, src, dst, **build):
+    import paper_1802_03760_amd as gj
+    ctx = gj.Context(0)
+    G = gj.Graph(ctx, src, dst, n, **build)
+    if build:
+        src, dst, _ = oracle.relabel_by_degree(n, src, dst, undirected=build.get("undirected", False))
+    O = oracle.Graph(n, src, dst)
+    for q in (Q.CLIQUE4, Q.CLIQUE5):
+        want = oracle.run(O, q, threads=8)
+        got = gj.count(ctx, G, gj.Query(ctx, *q))
+        for k in ("matches", "prefixes", "extensions"):
+            assert got[k] == want[k], (q[0], k, got[k], want[k])
+
+
+@pytest.mark.parametrize("k", [1, 2, 3, 63, 64, 65, 256, 257, 512, 513, 1056, 1057])
+def test_members(k):
+    """A vertex joined to k vertices of higher degree, in both directions and
+    some both ways, with some 20 edges among them each."""
+    rng = np.random.default_rng(k)
+    hubs = 1 + np.arange(k)
+    leaves = np.arange(k * (k + 8)) + 1 + k  # each hub's own, so that the first vertex has the least degree
+    s, d = [np.repeat(hubs, k + 8)], [leaves]
+    way = rng.integers(0, 3, k)  # out, in, both
+    s += [np.zeros(int((way != 1).sum()), int), hubs[way != 0]]
+    d += [hubs[way != 1], np.zeros(int((way != 0).sum()), int)]
+    if k > 1:
+        s.append(rng.integers(1, 1 + k, 20 * k))
+        d.append(rng.integers(1, 1 + k, 20 * k))
+    check(1 + k + len(leaves), np.concatenate(s).astype(np.uint32), np.concatenate(d).astype(np.uint32))
+
+
+@pytest.mark.parametrize("build", [{}, {"degree_order": True}, {"degree_order": True, "undirected": True}])
+def test_rmat(build):
+    s, d = synth.rmat_draws(10, 12, seed=2)
+    check(1 << 10, s, d, **build)
+
+
+def test_complete():
+    """Every ordered pair of 40 vertices: all members both ways."""
+    n = 40
+    s, d = np.nonzero(~np.eye(n, dtype=bool))
+    check(n, s.astype(np.uint32), d.astype(np.uint32))
