@@ -33,4 +33,23 @@ void owner_count(gj_ctx* c, const OwnerArgs& a, const uint32_t* seed_row, const 
                  uint64_t& extensions, int64_t* wsum = nullptr, OwnerPlan* plan = nullptr, uint64_t gen = 0,
                  gj_ctx* pc = nullptr);
 
+// Listing: a bit per value of every seed edge's proposing set.
+struct OwnerMask {
+  unsigned long long* mask = nullptr;
+  const uint32_t* woff = nullptr;     // E + 1: an edge's first word
+  const uint32_t* seed_of = nullptr;  // E: transposed entry -> seed edge
+};
+constexpr uint64_t kOwnerMaskMax = 4ull << 30;  // bytes of mask
+
+// The pairs of owner_count's sets, for listing: marks every match and numbers
+// the rows of every seed edge, in workspace (`words` of mask); matches and extensions as
+// owner_count (its plan, too).  False, and nothing marked, when the mask would
+// exceed kOwnerMaskMax.  owner_rows then writes the `matches` rows in seed and
+// value order, with their columns placed by map.
+bool owner_mask(gj_ctx* c, const OwnerArgs& a, const uint32_t* seed_row, const uint32_t* seed_col,
+                const uint32_t* t_row, const uint32_t* t_col, uint64_t E, KernelTimer& timer, OwnerPlan* plan,
+                uint64_t gen, gj_ctx* pc, uint64_t& words, uint64_t& matches, uint64_t& extensions);
+void owner_rows(gj_ctx* c, const OwnerArgs& a, const uint32_t* seed_row, const uint32_t* seed_col, uint64_t E,
+                uint64_t words, const RowMap& map, uint32_t* rows);
+
 }  // namespace gj

@@ -21,6 +21,13 @@
 // the (prefix, range) balancing of Sec. 3.4 applied within the GPU.  Probe
 // sets larger than half the table are processed in id-range segments.  Edges
 // whose larger set is below kDMin go to a per-edge merge in the same launch.
+//
+// Listing (owner_mask, owner_rows): the same pass sets a bit for every
+// proposed value that is in the other set, and the rows are written from the
+// bits in seed and value order.  R-MAT-20 triangles, 5.7e8 rows: 99.1 -> 11.8 ms
+// against the per-candidate kernels in 120 batches of 2^25 candidates, whose
+// searches and second resolution of every candidate were the bound; now the
+// LDS probes are (6.4 ms), then the rows' writes (4.1 ms).
 #include <algorithm>
 
 #include "gj_internal.h"
@@ -212,9 +219,12 @@ constexpr int kBufWord3 = 0x00020000;
 // keeps the test to a few full-rate instructions.  Values whose first bucket
 // is full and lacks them walk on to later buckets behind one wave-uniform
 // branch.
-template <int U>
+// MASK: the hits go to `words` instead, a bit per value (64 to a word), by
+// stores or, where another segment of the owner's set shares words, by or.
+template <int U, bool MASK>
 __device__ __forceinline__ uint32_t stream_probe(const uint32_t* __restrict__ set, uint32_t s, const uint32_t* H,
-                                                 int shift, uint32_t mask) {
+                                                 int shift, uint32_t mask, unsigned long long* __restrict__ words,
+                                                 bool shared) {
   const uint4* B = reinterpret_cast<const uint4*>(H);
   const uint32_t lane = (uint32_t)lane_id();
   // the wave's proposing set (wave-uniform base and size) as a raw buffer
@@ -240,11 +250,12 @@ __device__ __forceinline__ uint32_t stream_probe(const uint32_t* __restrict__ se
       b[u] = bucket_of(x[u], shift);
       q[u] = B[b[u]];
     }
-    uint32_t pend = 0;
+    uint32_t pend = 0, got = 0;
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       bool hit = min(min(q[u].x ^ x[u], q[u].y ^ x[u]), min(q[u].z ^ x[u], q[u].w ^ x[u])) == 0u;
       hits += (ok[u] & hit) ? 1u : 0u;
+      if (MASK) got |= (ok[u] & hit) ? (1u << u) : 0u;
       pend |= (ok[u] & !hit & (q[u].w != kEmpty)) ? (1u << u) : 0u;
     }
     // a full first bucket without the value: walk on (one wave-uniform branch)
@@ -259,8 +270,21 @@ __device__ __forceinline__ uint32_t stream_probe(const uint32_t* __restrict__ se
             uint4 r = B[bb];
             bool hit = min(min(r.x ^ x[u], r.y ^ x[u]), min(r.z ^ x[u], r.w ^ x[u])) == 0u;
             hits += hit ? 1u : 0u;
+            if (MASK) got |= hit ? (1u << u) : 0u;
             more = !hit & (r.w != kEmpty);
           }
+        }
+      }
+    }
+    if (MASK) {
+      // the lanes past the set's end left the loop; lane 0 takes every step
+      const uint64_t at = i >> 6;
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const unsigned long long w = __ballot((got >> u) & 1u);
+        if (lane == 0 && w) {
+          if (shared) atomicOr(words + at + u, w);
+          else words[at + u] = w;
         }
       }
     }
@@ -268,18 +292,23 @@ __device__ __forceinline__ uint32_t stream_probe(const uint32_t* __restrict__ se
   return hits;
 }
 
-// SIGNED: seed edges carry signs (a.sg0, a.sg1), acc[2] gets the signed sum
-template <bool SIGNED>
+// SIGNED: seed edges carry signs (a.sg0, a.sg1), acc[2] gets the signed sum.
+// MASK: for listing; every seed edge e has a (zeroed) bit per value of its
+// proposing set, words woff[e] .. woff[e + 1] of mask, set where the value is
+// in the other set (edges of the small-set loop propose LA(x0)); seed_of maps
+// transposed entries to seed edges.  Hits are not counted.
+template <bool SIGNED, bool MASK>
 __global__ void __launch_bounds__(kOwnNT) __attribute__((amdgpu_waves_per_eu(8))) k_owner_count(OwnerArgs a, const uint32_t* __restrict__ tasks,
                                                         uint32_t ntask, unsigned int* __restrict__ counter,
                                                         const uint32_t* __restrict__ seed_row,
                                                         const uint32_t* __restrict__ seed_col, uint64_t E,
-                                                        unsigned long long* __restrict__ acc) {
+                                                        unsigned long long* __restrict__ acc, OwnerMask om) {
   __shared__ __attribute__((aligned(16))) uint32_t H[kSlots];
   __shared__ uint32_t pst[kOwnNT];       // start of each partner's proposing set
   __shared__ uint32_t pval[kOwnNT + 1];  // long: size; short: offset in the short space
   __shared__ uint16_t wstart[kOwnNT];    // short window -> set holding its first element
-  __shared__ int8_t psg[kOwnNT];         // sign of each partner's seed edge
+  __shared__ int8_t psg[SIGNED ? kOwnNT : 1];     // sign of each partner's seed edge
+  __shared__ uint32_t pword[MASK ? kOwnNT : 1];  // first mask word of each partner's elements
   __shared__ uint32_t s_task, s_long;
   __shared__ uint32_t s_scan[kOwnNT / 64 + 1];
   __shared__ uint64_t s_sum[kOwnNT / 64 + 1];
@@ -306,6 +335,7 @@ __global__ void __launch_bounds__(kOwnNT) __attribute__((amdgpu_waves_per_eu(8))
       uint32_t i = c + tid;
       uint32_t qb = 0, s_full = 0;
       int8_t sg = 1;
+      uint32_t word = 0;
       if (i < phi) {
         if (SIGNED) sg = (r ? a.sg1 : a.sg0)[Sb + i];
         uint32_t u = L.sadj[Sb + i];
@@ -313,6 +343,7 @@ __global__ void __launch_bounds__(kOwnNT) __attribute__((amdgpu_waves_per_eu(8))
         s_full = L.qrp[u + 1] - qb;
         if (!owned(r, s_full, D)) s_full = 0;
         ext += s_full;
+        if (MASK && s_full) word = om.woff[r ? om.seed_of[Sb + i] : Sb + i];
       }
       uint32_t cur = qb;  // first element of the proposing set not yet given to a segment
       for (uint32_t seg = 0; seg < nseg; ++seg) {
@@ -335,7 +366,9 @@ __global__ void __launch_bounds__(kOwnNT) __attribute__((amdgpu_waves_per_eu(8))
           uint32_t end = qb + s_full;
           // vertex ids are below 2^32 - 1, so hi_s + 1 does not wrap
           uint32_t b1 = seg + 1 == nseg ? end : gallop_lb(L.qadj, cur, end, L.padj[Lb + e1 - 1] + 1);
-          s = b1 - cur;
+          // whole mask words: the elements before cur miss here
+          if (MASK) st = qb + ((cur - qb) & ~63u);
+          s = b1 == cur ? 0 : b1 - st;
           cur = b1;
         }
         // one scan: long-partner count in the high half, short sizes in the low half
@@ -348,12 +381,14 @@ __global__ void __launch_bounds__(kOwnNT) __attribute__((amdgpu_waves_per_eu(8))
           pst[kl] = st;
           pval[kl] = s;
           if (SIGNED) psg[kl] = sg;
+          if (MASK) pword[kl] = word + ((st - qb) >> 6);
         } else {
           uint32_t j = nlong + ((uint32_t)tid - kl);
           uint32_t off = pre & 0xFFFFu;
           pst[j] = st;
           pval[j] = off;
           if (SIGNED) psg[j] = sg;
+          if (MASK) pword[j] = word + ((st - qb) >> 6);
           // the windows of 64 short elements that start inside this set
           for (uint32_t w = (off + 63) >> 6; (w << 6) < off + s; ++w) wstart[w] = (uint16_t)j;
         }
@@ -373,12 +408,13 @@ __global__ void __launch_bounds__(kOwnNT) __attribute__((amdgpu_waves_per_eu(8))
           uint32_t s_k = __builtin_amdgcn_readfirstlane(pval[k]);
           // loads per step by set size: fewer wasted lanes on short sets
           uint32_t h;
+          unsigned long long* words = MASK ? om.mask + __builtin_amdgcn_readfirstlane(pword[MASK ? k : 0]) : nullptr;
           if (s_k <= 128)
-            h = stream_probe<2>(L.qadj + st_k, s_k, H, shift, mask);
+            h = stream_probe<2, MASK>(L.qadj + st_k, s_k, H, shift, mask, words, nseg > 1);
           else if (s_k <= 192)
-            h = stream_probe<3>(L.qadj + st_k, s_k, H, shift, mask);
+            h = stream_probe<3, MASK>(L.qadj + st_k, s_k, H, shift, mask, words, nseg > 1);
           else
-            h = stream_probe<4>(L.qadj + st_k, s_k, H, shift, mask);
+            h = stream_probe<4, MASK>(L.qadj + st_k, s_k, H, shift, mask, words, nseg > 1);
           hits += h;
           if (SIGNED) shits += (int64_t)psg[k] * h;
         }
@@ -386,13 +422,28 @@ __global__ void __launch_bounds__(kOwnNT) __attribute__((amdgpu_waves_per_eu(8))
         // lane starts from the set holding its window's first element
         for (uint32_t g0 = (uint32_t)wave * 64; g0 < short_total; g0 += nwaves * 64) {
           uint32_t g = g0 + lane;
+          uint32_t p = 0, k = 0;
+          bool hit = false;
           if (g < short_total) {
-            uint32_t p = wstart[g0 >> 6];
+            p = wstart[g0 >> 6];
             while (pval[p + 1] <= g) ++p;
-            uint32_t x = L.qadj[pst[p] + (g - pval[p])];
-            bool hit = probe(H, x, shift, mask);
+            k = g - pval[p];
+            uint32_t x = L.qadj[pst[p] + k];
+            hit = probe(H, x, shift, mask);
             hits += hit ? 1 : 0;
             if (SIGNED) shits += hit ? psg[p] : 0;
+          }
+          if (MASK) {
+            // a set's elements here are consecutive lanes from the lane of its
+            // element kf on; the first of them writes the set's hits.  A set
+            // may start in the window before this one, so by or.
+            const uint64_t hb = __ballot(hit);
+            const uint32_t pp = __shfl_up(p, 1, 64);
+            if (hb && g < short_total && (lane == 0 || pp != p)) {
+              const uint32_t n = min(pval[p + 1] - pval[p] - k, 64u - lane);
+              const uint64_t mine = (hb >> lane) & (n == 64 ? ~0ull : (1ull << n) - 1);
+              if (mine) atomicOr(om.mask + pword[MASK ? p : 0], (unsigned long long)mine << k);
+            }
           }
         }
         __syncthreads();
@@ -452,8 +503,10 @@ __global__ void __launch_bounds__(kOwnNT) __attribute__((amdgpu_waves_per_eu(8))
           if (y < va[t]) pos += step;
         }
         uint32_t at = (uint32_t)__shfl((int)vb[t], (int)pos, 64);
-        uint32_t eh = (uint32_t)__popcll(__ballot((uint32_t)lane < na[t] && at == va[t]));
+        const uint64_t eb = __ballot((uint32_t)lane < na[t] && at == va[t]);
+        uint32_t eh = (uint32_t)__popcll(eb);
         if (lane == 0) {
+          if (MASK && eb) om.mask[om.woff[e0 + src[t]]] = eb;
           hits += eh;
           if (SIGNED) shits += (int64_t)a.sg0[e0 + src[t]] * eh;
         }
@@ -473,12 +526,171 @@ __global__ void __launch_bounds__(kOwnNT) __attribute__((amdgpu_waves_per_eu(8))
   }
 }
 
+// ---------------------------------------------------------------- listing
+// Which set of a seed edge proposes, and its size: LB(x1) unless LA(x0) is
+// smaller, as the units own edges; LA(x0) in the small-set loop.
+__device__ __forceinline__ bool proposes_b(uint32_t da, uint32_t db) {
+  return (da > db ? da : db) >= kDMin && db <= da;
+}
+
+__global__ void k_mask_words(OwnerArgs a, const uint32_t* __restrict__ row, const uint32_t* __restrict__ col,
+                             uint64_t E, uint32_t* __restrict__ words) {
+  const uint64_t gs = (uint64_t)gridDim.x * blockDim.x;
+  for (uint64_t e = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; e < E; e += gs) {
+    const uint32_t da = a.rpA[row[e] + 1] - a.rpA[row[e]], db = a.rpB[col[e] + 1] - a.rpB[col[e]];
+    const uint32_t s = !da || !db ? 0 : proposes_b(da, db) ? db : da;
+    words[e] = s / 64 + (s % 64 != 0);
+  }
+}
+
+// seed edge (x0, v) of every transposed entry (v, x0) whose unit, (v, 1), may
+// own it
+__global__ void k_seed_of(OwnerArgs a, const uint32_t* __restrict__ t_row, const uint32_t* __restrict__ t_col,
+                          uint64_t E, uint32_t* __restrict__ seed_of) {
+  const uint64_t gs = (uint64_t)gridDim.x * blockDim.x;
+  for (uint64_t e = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; e < E; e += gs) {
+    const uint32_t v = t_row[e], x0 = t_col[e];
+    const uint32_t db = a.rpB[v + 1] - a.rpB[v];
+    if (db < kDMin || a.rpA[x0 + 1] - a.rpA[x0] >= db) continue;
+    seed_of[e] = lower_bound_u32(a.adjS0, a.rpS0[x0], a.rpS0[x0 + 1], v);
+  }
+}
+
+// hits of every edge: a lane per edge, the long ones by the whole wave
+__global__ void __launch_bounds__(kBlock) k_mask_count(const unsigned long long* __restrict__ mask,
+                                                       const uint32_t* __restrict__ woff, uint64_t E,
+                                                       uint32_t* __restrict__ cnt) {
+  constexpr uint32_t kAlone = 4;
+  const int lane = lane_id();
+  const uint64_t gw = (uint64_t)gridDim.x * (kBlock / 64);
+  for (uint64_t b = ((uint64_t)blockIdx.x * (kBlock / 64) + wave_id()) * 64; b < E; b += gw * 64) {
+    const uint64_t e = b + lane;
+    uint32_t w = 0, n = 0, t = 0;
+    if (e < E) {
+      w = woff[e];
+      n = woff[e + 1] - w;
+    }
+    if (n <= kAlone)
+      for (uint32_t i = 0; i < n; ++i) t += (uint32_t)__popcll(mask[(uint64_t)w + i]);
+    for (uint64_t big = __ballot(n > kAlone); big; big &= big - 1) {
+      const int src = __ffsll((unsigned long long)big) - 1;
+      const uint32_t ws = __shfl(w, src, 64), ns = __shfl(n, src, 64);
+      uint64_t s = 0;
+      for (uint32_t i = lane; i < ns; i += 64) s += (uint64_t)__popcll(mask[(uint64_t)ws + i]);
+      s = wave_sum(s);
+      if (lane == src) t = (uint32_t)s;
+    }
+    if (e < E) cnt[e] = t;
+  }
+}
+
+// Rows (x0, x1, value) of all matches: rows are numbered in the order of the
+// mask's words and bits.  A wave takes kRowWords words, 64 at a time: each
+// lane finds its word's edge and lists its hits in LDS, then the lanes write
+// one row each.  About one bit in seven is set (R-MAT-20), so going through
+// the words a word per step, 64 lanes to it, was issue-bound: 6.8 GB of rows
+// in 6.6 ms -> 4.1 ms.
+constexpr uint32_t kRowWords = 512;
+
+struct Row3 {
+  uint32_t v[3];
+};
+
+__global__ void __launch_bounds__(kBlock) k_mask_rows(OwnerArgs a, const uint32_t* __restrict__ row,
+                                                      const uint32_t* __restrict__ col,
+                                                      const unsigned long long* __restrict__ mask,
+                                                      const uint32_t* __restrict__ woff,
+                                                      const uint64_t* __restrict__ off, uint64_t E, uint32_t nw,
+                                                      RowMap map, uint32_t* __restrict__ rows) {
+  __shared__ uint16_t list_s[kBlock / 64][64 * 64];
+  uint16_t* list = list_s[wave_id()];
+  const uint32_t lane = lane_id();
+  const int c0 = map.attr[0], c1 = map.attr[1];
+  const uint32_t wlo = (blockIdx.x * (kBlock / 64) + wave_id()) * kRowWords;  // fewer than 2^29 words
+  if (wlo >= nw) return;
+  const uint32_t whi = nw - wlo < kRowWords ? nw : wlo + kRowWords;
+  // the edge of word wlo: the last with woff[e] <= wlo, by 64-way search
+  uint64_t elo = 0, ehi = E;  // woff[elo] <= wlo < woff[ehi]
+  while (ehi - elo > 1) {
+    const uint64_t step = (ehi - elo + 63) / 64, at = elo + lane * step;
+    const uint64_t below = __ballot(at < ehi && woff[at] <= wlo);  // lane 0 always
+    const int k = 63 - __clzll((long long)below);
+    elo += k * step;
+    ehi = elo + step < ehi ? elo + step : ehi;
+  }
+  // the row of word wlo: the edge's first and those of its words before
+  uint64_t r0 = 0;
+  for (uint64_t i = (uint64_t)woff[elo] + lane; i < wlo; i += 64) r0 += (uint64_t)__popcll(mask[i]);
+  r0 = off[elo] + wave_sum(r0);
+  for (uint32_t w0 = wlo; w0 < whi; w0 += 64) {
+    const uint32_t w = w0 + lane;
+    const bool live = w < whi;
+    uint64_t m = live ? mask[w] : 0;
+    // the edge of the lane's word: woff[lo] <= w < woff[hi], by doubling steps
+    uint64_t lo = elo;
+    if (live) {
+      uint64_t step = 1, hi = lo + 1;
+      while (hi < E && woff[hi] <= w) {
+        lo = hi;
+        step <<= 1;
+        hi = lo + step;
+      }
+      if (hi > E) hi = E;
+      while (hi - lo > 1) {
+        const uint64_t mid = (lo + hi) >> 1;
+        if (woff[mid] <= w) lo = mid;
+        else hi = mid;
+      }
+    }
+    elo = shfl_u64(lo, (int)(whi - w0 < 64 ? whi - w0 : 64) - 1);
+    uint32_t x0 = 0, x1 = 0, start = 0;
+    bool from_b = false;
+    if (m) {
+      x0 = row[lo];
+      x1 = col[lo];
+      from_b = proposes_b(a.rpA[x0 + 1] - a.rpA[x0], a.rpB[x1 + 1] - a.rpB[x1]);
+      start = (from_b ? a.rpB[x1] : a.rpA[x0]) + (w - woff[lo]) * 64;
+    }
+    const uint64_t bs = __ballot(from_b);
+    const uint32_t pc = (uint32_t)__popcll(m), incl = wave_incl_scan(pc);
+    const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+    for (uint32_t at = incl - pc; m; m &= m - 1) list[at++] = (uint16_t)(lane * 64 + __builtin_ctzll(m));
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    for (uint32_t t = 0; t < total; t += 64) {  // whole waves: the shuffles read every lane's word
+      const bool mine = t + lane < total;
+      const uint32_t p = mine ? list[t + lane] : 0, src = p >> 6;
+      const uint32_t y0 = __shfl(x0, src, 64), y1 = __shfl(x1, src, 64), s = __shfl(start, src, 64);
+      if (mine) {
+        const uint32_t x = ((bs >> src) & 1 ? a.adjB : a.adjA)[(uint64_t)s + (p & 63)];
+        const Row3 o{{c0 == 0 ? y0 : c1 == 0 ? y1 : x, c0 == 1 ? y0 : c1 == 1 ? y1 : x,
+                      c0 == 2 ? y0 : c1 == 2 ? y1 : x}};
+        *(Row3*)(rows + (r0 + t + lane) * 3) = o;
+      }
+    }
+    r0 += total;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  }
+}
+
 // ---------------------------------------------------------------- host
-void owner_count(gj_ctx* c, const OwnerArgs& a, const uint32_t* seed_row, const uint32_t* seed_col,
-                 const uint32_t* t_row, const uint32_t* t_col, uint64_t E, KernelTimer& timer, uint64_t& matches,
-                 uint64_t& extensions, int64_t* wsum, OwnerPlan* plan, uint64_t gen, gj_ctx* pc) {
+// The tasks of a launch (kept with the version, or planned now) and the
+// counters it starts from: acc (matches, extensions, signed sum, units split
+// into several tasks) and the task counter, both zeroed.
+struct OwnerLaunch {
+  unsigned long long* acc;
+  unsigned int* counter;
+  const uint32_t* tasks;
+  uint64_t nt;
+};
+
+static OwnerLaunch owner_launch(gj_ctx* c, const OwnerArgs& a, const uint32_t* seed_row, const uint32_t* seed_col,
+                                const uint32_t* t_row, const uint32_t* t_col, uint64_t E, OwnerPlan* plan,
+                                uint64_t gen, gj_ctx* pc) {
   uint64_t units = 2ull * a.n;
-  // acc: matches, extensions, signed sum, units split into several tasks
   unsigned long long* acc = (unsigned long long*)ws_get(c, "own_acc", 4 * sizeof(unsigned long long));
   unsigned int* counter = (unsigned int*)ws_get(c, "own_ctr", sizeof(unsigned int));
   GJ_HIP(hipMemsetAsync(acc, 0, 4 * sizeof(unsigned long long), c->stream));
@@ -538,22 +750,78 @@ void owner_count(gj_ctx* c, const OwnerArgs& a, const uint32_t* seed_row, const 
       plan->gen = gen;
     }
   }
+  c->owner_tasks = nt;
+  c->owner_split_units = split;
+  return OwnerLaunch{acc, counter, tasks, nt};
+}
+
+void owner_count(gj_ctx* c, const OwnerArgs& a, const uint32_t* seed_row, const uint32_t* seed_col,
+                 const uint32_t* t_row, const uint32_t* t_col, uint64_t E, KernelTimer& timer, uint64_t& matches,
+                 uint64_t& extensions, int64_t* wsum, OwnerPlan* plan, uint64_t gen, gj_ctx* pc) {
+  const OwnerLaunch l = owner_launch(c, a, seed_row, seed_col, t_row, t_col, E, plan, gen, pc);
   unsigned grid = (unsigned)c->num_cus * 2;
   timer.start();
   GJ_CHECK((a.sg0 == nullptr) == (a.sg1 == nullptr), GJ_EINVAL, "owner kernel: signs for one order only");
   if (a.sg0)
-    k_owner_count<true><<<grid, kOwnNT, 0, c->stream>>>(a, tasks, (uint32_t)nt, counter, seed_row, seed_col, E, acc);
+    k_owner_count<true, false><<<grid, kOwnNT, 0, c->stream>>>(a, l.tasks, (uint32_t)l.nt, l.counter, seed_row,
+                                                               seed_col, E, l.acc, OwnerMask{});
   else
-    k_owner_count<false><<<grid, kOwnNT, 0, c->stream>>>(a, tasks, (uint32_t)nt, counter, seed_row, seed_col, E, acc);
+    k_owner_count<false, false><<<grid, kOwnNT, 0, c->stream>>>(a, l.tasks, (uint32_t)l.nt, l.counter, seed_row,
+                                                                seed_col, E, l.acc, OwnerMask{});
   timer.stop();
   GJ_HIP(hipGetLastError());
   unsigned long long h[3];
-  read_bytes(c, h, acc, sizeof(h));
-  c->owner_tasks = nt;
-  c->owner_split_units = split;
+  read_bytes(c, h, l.acc, sizeof(h));
   matches = h[0];
   extensions = h[1];
   if (wsum) *wsum = a.sg0 ? (int64_t)h[2] : (int64_t)h[0];
+}
+
+bool owner_mask(gj_ctx* c, const OwnerArgs& a, const uint32_t* seed_row, const uint32_t* seed_col,
+                const uint32_t* t_row, const uint32_t* t_col, uint64_t E, KernelTimer& timer, OwnerPlan* plan,
+                uint64_t gen, gj_ctx* pc, uint64_t& nw, uint64_t& matches, uint64_t& extensions) {
+  nw = matches = extensions = 0;
+  if (!E) return true;
+  uint32_t* words = (uint32_t*)ws_get(c, "om_words", (E + 1) * sizeof(uint32_t));
+  uint32_t* woff = (uint32_t*)ws_get(c, "om_woff", (E + 1) * sizeof(uint32_t));
+  uint64_t* off = (uint64_t*)ws_get(c, "om_off", (E + 1) * sizeof(uint64_t));
+  const unsigned ge = grid_for(E, kBlock * 4, 1u << 14);
+  // 64-bit offsets first (in the row offsets' buffer): the words may exceed 32 bits
+  k_mask_words<<<ge, kBlock, 0, c->stream>>>(a, seed_row, seed_col, E, words);
+  scan_u32_to_u64(c, words, off, E);
+  nw = read_u64(c, off + E);
+  if (nw * sizeof(uint64_t) > kOwnerMaskMax) return false;
+  scan_u32(c, words, woff, E);
+  unsigned long long* mask = (unsigned long long*)ws_get(c, "om_mask", (nw + 1) * sizeof(uint64_t));
+  uint32_t* seed_of = (uint32_t*)ws_get(c, "om_seed", (E + 1) * sizeof(uint32_t));
+  GJ_HIP(hipMemsetAsync(mask, 0, nw * sizeof(uint64_t), c->stream));
+  const OwnerLaunch l = owner_launch(c, a, seed_row, seed_col, t_row, t_col, E, plan, gen, pc);
+  k_seed_of<<<ge, kBlock, 0, c->stream>>>(a, t_row, t_col, E, seed_of);
+  timer.start();
+  k_owner_count<false, true><<<(unsigned)c->num_cus * 2, kOwnNT, 0, c->stream>>>(
+      a, l.tasks, (uint32_t)l.nt, l.counter, seed_row, seed_col, E, l.acc, OwnerMask{mask, woff, seed_of});
+  timer.stop();
+  k_mask_count<<<grid_for(E, kBlock, (unsigned)c->num_cus * 32), kBlock, 0, c->stream>>>(mask, woff, E, words);
+  scan_u32_to_u64(c, words, off, E);
+  GJ_HIP(hipGetLastError());
+  uint64_t h[2];
+  read_u64s(c, {off + E, (const uint64_t*)(l.acc + 1)}, h);
+  matches = h[0];
+  extensions = h[1];
+  return true;
+}
+
+void owner_rows(gj_ctx* c, const OwnerArgs& a, const uint32_t* seed_row, const uint32_t* seed_col, uint64_t E,
+                uint64_t words, const RowMap& map, uint32_t* rows) {
+  if (!words) return;
+  // as owner_mask left them
+  const unsigned long long* mask = (const unsigned long long*)ws_get(c, "om_mask", 0);
+  const uint32_t* woff = (const uint32_t*)ws_get(c, "om_woff", 0);
+  const uint64_t* off = (const uint64_t*)ws_get(c, "om_off", 0);
+  const uint32_t nw = (uint32_t)words;
+  k_mask_rows<<<(nw + kRowWords * (kBlock / 64) - 1) / (kRowWords * (kBlock / 64)), kBlock, 0, c->stream>>>(
+      a, seed_row, seed_col, mask, woff, off, E, nw, map, rows);
+  GJ_HIP(hipGetLastError());
 }
 
 }  // namespace gj
