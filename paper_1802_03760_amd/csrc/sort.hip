@@ -1,13 +1,23 @@
 // Stable LSD radix sort, 8-bit digits.  Each pass: per-tile digit histogram,
-// exclusive scan of the digit-major histogram, stable scatter (ranks within a
-// wave from eight ballots, across waves and items through LDS counters).
+// exclusive scan of the digit-major histogram, stable scatter.
+//
+// A tile is kSortNT x kSortItems consecutive keys, a contiguous share of them
+// to each wave.  The scatter ranks a wave's keys digit by digit without
+// leaving the wave (eight ballots name the lanes with the same digit, a
+// wave-private LDS counter carries the running count), then places the tile's
+// keys in digit order in LDS and writes them out from there, 16 keys of a digit
+// in a row on average.  Both kernels are bound by memory: 67.5e6 keys, scatter
+// 525 -> 257 us, histogram 178 -> 138 us against a tile of 2,048
+// ranked in eight block-wide steps and written straight from registers.
 #include "gj_internal.h"
 #include "prim.h"
 
 namespace gj {
 
+constexpr int kSortNT = 512;
 constexpr int kSortItems = 8;
-constexpr int kSortTile = kBlock * kSortItems;
+constexpr int kSortWaves = kSortNT / 64;
+constexpr int kSortTile = kSortNT * kSortItems;
 constexpr int kRadix = 256;
 
 template <typename K>
@@ -15,70 +25,120 @@ __device__ __forceinline__ uint32_t digit_of(K k, int shift) {
   return (uint32_t)(k >> shift) & 0xFFu;
 }
 
+__device__ __forceinline__ void wave_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 template <typename K>
-__global__ void __launch_bounds__(kBlock) k_hist(const K* __restrict__ keys, uint64_t n, int shift,
-                                                 uint32_t* __restrict__ hist, uint32_t ntiles) {
-  __shared__ uint32_t h[kRadix];
-  h[threadIdx.x] = 0;
+__global__ void __launch_bounds__(kSortNT) k_hist(const K* __restrict__ keys, uint64_t n, int shift,
+                                                  uint32_t* __restrict__ hist, uint32_t ntiles) {
+  __shared__ uint32_t h[kSortWaves][kRadix];
+  const int wave = wave_id();
+  for (int i = threadIdx.x; i < kSortWaves * kRadix; i += kSortNT) (&h[0][0])[i] = 0;
   __syncthreads();
-  uint64_t base = (uint64_t)blockIdx.x * kSortTile;
+  const uint64_t base = (uint64_t)blockIdx.x * kSortTile;
+  K k[kSortItems];
 #pragma unroll
   for (int i = 0; i < kSortItems; ++i) {
-    uint64_t idx = base + (uint64_t)i * kBlock + threadIdx.x;
-    if (idx < n) atomicAdd(&h[digit_of(keys[idx], shift)], 1u);
+    const uint64_t idx = base + (uint64_t)i * kSortNT + threadIdx.x;
+    k[i] = idx < n ? keys[idx] : (K)0;
   }
+#pragma unroll
+  for (int i = 0; i < kSortItems; ++i)
+    if (base + (uint64_t)i * kSortNT + threadIdx.x < n) atomicAdd(&h[wave][digit_of(k[i], shift)], 1u);
   __syncthreads();
-  hist[(uint64_t)threadIdx.x * ntiles + blockIdx.x] = h[threadIdx.x];
+  if (threadIdx.x < kRadix) {
+    uint32_t t = 0;
+#pragma unroll
+    for (int w = 0; w < kSortWaves; ++w) t += h[w][threadIdx.x];
+    hist[(uint64_t)threadIdx.x * ntiles + blockIdx.x] = t;
+  }
 }
 
 template <typename K, bool VAL>
-__global__ void __launch_bounds__(kBlock) k_scatter(const K* __restrict__ keys, const uint32_t* __restrict__ vals,
-                                                    uint64_t n, int shift,
-                                                    const uint32_t* __restrict__ hist_off, uint32_t ntiles,
-                                                    K* __restrict__ okeys, uint32_t* __restrict__ ovals) {
-  __shared__ uint32_t base_cnt[kRadix];        // running count per digit in this tile
-  __shared__ uint32_t wcnt[kBlock / 64][kRadix];
-  const int lane = lane_id(), wave = wave_id();
-  base_cnt[threadIdx.x] = hist_off[(uint64_t)threadIdx.x * ntiles + blockIdx.x];
-  uint64_t base = (uint64_t)blockIdx.x * kSortTile;
-  for (int i = 0; i < kSortItems; ++i) {
+__global__ void __launch_bounds__(kSortNT) k_scatter(const K* __restrict__ keys, const uint32_t* __restrict__ vals,
+                                                     uint64_t n, int shift,
+                                                     const uint32_t* __restrict__ hist_off, uint32_t ntiles,
+                                                     K* __restrict__ okeys, uint32_t* __restrict__ ovals) {
+  __shared__ K tile[kSortTile];
+  __shared__ uint32_t tval[VAL ? kSortTile : 1];
+  __shared__ uint32_t wcnt[kSortWaves][kRadix];  // running counts, then first places, per wave and digit
+  __shared__ uint32_t goff[kRadix];              // a digit's first output place less its first tile place
+  __shared__ uint32_t part[kRadix / 64];
+  const int lane = lane_id(), wave = wave_id(), tid = threadIdx.x;
+  for (int i = tid; i < kSortWaves * kRadix; i += kSortNT) (&wcnt[0][0])[i] = 0;
+  const uint64_t base = (uint64_t)blockIdx.x * kSortTile;
+  const uint64_t mine = base + (uint64_t)wave * (64 * kSortItems);
+  K k[kSortItems];
+  uint32_t v[kSortItems], at[kSortItems];
 #pragma unroll
-    for (int w = 0; w < kBlock / 64; ++w) wcnt[w][threadIdx.x] = 0;
-    __syncthreads();
-    uint64_t idx = base + (uint64_t)i * kBlock + threadIdx.x;
-    bool valid = idx < n;
-    K k = valid ? keys[idx] : (K)0;
-    uint32_t v = 0;
-    if (VAL && valid) v = vals[idx];
-    uint32_t d = digit_of(k, shift);
+  for (int i = 0; i < kSortItems; ++i) {
+    const uint64_t idx = mine + (uint64_t)i * 64 + lane;
+    k[i] = idx < n ? keys[idx] : (K)0;
+    v[i] = VAL && idx < n ? vals[idx] : 0;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < kSortItems; ++i) {
+    const bool valid = mine + (uint64_t)i * 64 + lane < n;
+    const uint32_t d = digit_of(k[i], shift);
     uint64_t peers = __ballot(valid);
 #pragma unroll
     for (int b = 0; b < 8; ++b) {
-      uint64_t m = __ballot((d >> b) & 1u);
+      const uint64_t m = __ballot((d >> b) & 1u);
       peers &= ((d >> b) & 1u) ? m : ~m;
     }
-    uint32_t rank = __popcll(peers & lanemask_lt());
-    bool leader = valid && rank == 0;
-    if (leader) wcnt[wave][d] = __popcll(peers);
-    __syncthreads();
-    {
-      // one thread per digit: exclusive offsets across waves, advance base
-      uint32_t run = base_cnt[threadIdx.x];
+    const uint32_t rank = (uint32_t)__popcll(peers & lanemask_lt());
+    const uint32_t before = valid ? wcnt[wave][d] : 0;
+    at[i] = before + rank;
+    // every lane has read before the first lane of each digit adds, and the
+    // next step reads after
+    wave_fence();
+    if (valid && rank == 0) wcnt[wave][d] = before + (uint32_t)__popcll(peers);
+    wave_fence();
+  }
+  __syncthreads();
+  // a thread per digit: the digits' places in the tile, waves in order
+  uint32_t total = 0, incl = 0;
+  if (tid < kRadix) {
 #pragma unroll
-      for (int w = 0; w < kBlock / 64; ++w) {
-        uint32_t t = wcnt[w][threadIdx.x];
-        wcnt[w][threadIdx.x] = run;
-        run += t;
-      }
-      base_cnt[threadIdx.x] = run;
+    for (int w = 0; w < kSortWaves; ++w) total += wcnt[w][tid];
+    incl = wave_incl_scan(total);
+    if (lane == 63) part[wave] = incl;
+  }
+  __syncthreads();
+  if (tid < kRadix) {
+    uint32_t run = incl - total;
+    for (int w = 0; w < wave; ++w) run += part[w];
+    goff[tid] = hist_off[(uint64_t)tid * ntiles + blockIdx.x] - run;
+#pragma unroll
+    for (int w = 0; w < kSortWaves; ++w) {
+      const uint32_t t = wcnt[w][tid];
+      wcnt[w][tid] = run;
+      run += t;
     }
-    __syncthreads();
-    if (valid) {
-      uint32_t pos = wcnt[wave][d] + rank;
-      okeys[pos] = k;
-      if (VAL) ovals[pos] = v;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < kSortItems; ++i)
+    if (mine + (uint64_t)i * 64 + lane < n) {
+      const uint32_t p = wcnt[wave][digit_of(k[i], shift)] + at[i];
+      tile[p] = k[i];
+      if (VAL) tval[p] = v[i];
     }
-    __syncthreads();
+  __syncthreads();
+  const uint32_t cnt = n - base < (uint64_t)kSortTile ? (uint32_t)(n - base) : kSortTile;
+#pragma unroll
+  for (int i = 0; i < kSortItems; ++i) {
+    const uint32_t p = i * kSortNT + tid;
+    if (p < cnt) {
+      const K x = tile[p];
+      const uint32_t o = goff[digit_of(x, shift)] + p;
+      okeys[o] = x;
+      if (VAL) ovals[o] = tval[p];
+    }
   }
 }
 
@@ -131,10 +191,9 @@ static void radix_pass(gj_ctx* c, const K* keys, const uint32_t* vals, K* okeys,
   GJ_CHECK(nt * kRadix < (1ull << 32), GJ_EUNSUPPORTED, "sort too large");
   uint32_t* hist = (uint32_t*)ws_get(c, "sort_hist", nt * kRadix * sizeof(uint32_t));
   uint32_t* hoff = (uint32_t*)ws_get(c, "sort_hoff", (nt * kRadix + 1) * sizeof(uint32_t));
-  k_hist<K><<<(unsigned)nt, kBlock, 0, c->stream>>>(keys, n, shift, hist, (uint32_t)nt);
+  k_hist<K><<<(unsigned)nt, kSortNT, 0, c->stream>>>(keys, n, shift, hist, (uint32_t)nt);
   scan_u32(c, hist, hoff, nt * kRadix);
-  k_scatter<K, VAL><<<(unsigned)nt, kBlock, 0, c->stream>>>(keys, vals, n, shift, hoff,
-                                                             (uint32_t)nt, okeys, ovals);
+  k_scatter<K, VAL><<<(unsigned)nt, kSortNT, 0, c->stream>>>(keys, vals, n, shift, hoff, (uint32_t)nt, okeys, ovals);
   GJ_HIP(hipGetLastError());
 }
 
