@@ -2,6 +2,7 @@
 // delta entry points.
 #pragma once
 
+#include <utility>
 #include <vector>
 
 #include "gj_internal.h"
@@ -33,6 +34,7 @@ struct PlanH {
   // run, so counts may multiply), else 0
   int fact_from = 0;
   int ntri = 0;  // ternary atoms
+  std::vector<std::pair<int, int>> edges;  // positions (source, destination) of the binary atoms
   bool has_ineq() const {
     for (int j = 0; j < m; ++j)
       if (above[j] | below[j]) return true;
@@ -99,6 +101,7 @@ class Runner {
   void stage(int j, uint64_t n);
   StageDesc desc(int j, int lvl);
   void factorised(int j0, uint64_t n);
+  bool by_pair(int j, uint64_t n, uint64_t W);
   void ensure_rows(uint64_t need);
   Level L[GJ_MAX_ATTRS + 1];
   RowMap map;
@@ -106,6 +109,8 @@ class Runner {
   uint32_t* seed_flags = nullptr;
   uint64_t* seed_off = nullptr;
   bool rows_owned = false, signs_owned = false, want_signs = false;
+  const uint32_t* pair_cnt = nullptr;  // by_pair's counts per edge, once built
+  uint64_t pair_declined = 0;          // candidates of the largest batch that did not pay for them
 };
 
 }  // namespace gj

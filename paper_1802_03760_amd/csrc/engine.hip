@@ -27,6 +27,7 @@ PlanH make_plan(const gj_query* q, const std::vector<int>& order, int forced_see
   for (int i = 0; i < (int)q->atoms.size(); ++i) {
     int s = q->atoms[i].src_attr, d = q->atoms[i].dst_attr;
     int j = std::max(pos[s], pos[d]);
+    P.edges.push_back({pos[s], pos[d]});
     if (j == 1) {
       bool is_seed = forced_seed >= 0 ? i == forced_seed : P.seed_atom < 0;
       if (is_seed) {
@@ -304,6 +305,7 @@ void Runner::stage(int j, uint64_t n) {
   uint64_t W = read_u64(c, l.off + n);
   st.extensions[j] += W;
   if (W == 0) return;
+  if (j + 1 == P.m && by_pair(j, n, W)) return;
   // a static read that tests membership counts its candidates towards the
   // version's index, built once they pay for it (the records are written
   // again to name the new tables; the counts do not change)
@@ -360,6 +362,52 @@ void Runner::stage(int j, uint64_t n) {
       stage(j + 1, T);
     }
   }
+}
+
+// The last stage of a static count whose attribute is bound by two atoms, on
+// columns that another atom joins (the house's a5, bound by a2 and a3): a
+// prefix's survivors are a function of that edge, the common members of its
+// ends' sets.  They are counted once per edge, by the owner-grouped pass, and
+// summed over the prefixes, when the stage has at least kPairGain times the
+// candidates that takes (a word of 64 per edge and part of its smaller set).
+// House: 4.55 ms of run kernels (a shared set rebuilt for every a1) -> 0.15 ms
+// at R-MAT with 4,099 vertices, the whole query 76.4 -> 10.0 ms at 16,379;
+// uniform random graphs to 9.6e6 edges stay below the line and as they were.
+constexpr uint64_t kPairGain = 2;
+
+bool Runner::by_pair(int j, uint64_t n, uint64_t W) {
+  const std::vector<BindH>& b = P.bind[j];
+  if (collect || weighted || V.delta_atom >= 0 || !V.graph || c->arena.on || !c->run_stage || c->strategy == 1 ||
+      W < c->run_stage_min || P.above[j] || P.below[j] || b.size() != 2 || b[0].col2 >= 0 || b[1].col2 >= 0 ||
+      b[0].col == b[1].col)
+    return false;
+  const Version& v = *V.old_v;
+  if (v.pmap[0] || v.pmap[1] || W <= pair_declined) return false;
+  int x = -1, y = -1;  // columns of an edge x -> y among the two
+  for (const auto& e : P.edges)
+    if ((e.first == b[0].col && e.second == b[1].col) || (e.first == b[1].col && e.second == b[0].col)) {
+      x = e.first;
+      y = e.second;
+    }
+  if (x < 0) return false;
+  if (!pair_cnt) {
+    const BindH &A = b[0].col == x ? b[0] : b[1], &Bd = b[0].col == x ? b[1] : b[0];
+    OwnerArgs a{v.d[A.dir].rp, v.d[A.dir].col, v.d[Bd.dir].rp, v.d[Bd.dir].col,
+                v.d[0].rp,     v.d[0].col,     v.d[1].rp,      v.d[1].col,      V.graph->n};
+    uint64_t words = 0, matches = 0, ext = 0;
+    const uint64_t most = std::min(kOwnerMaskMax / 8, W / (64 * kPairGain));
+    if (!owner_mask(c, a, v.d[0].row, v.d[0].col, v.d[1].row, v.d[1].col, v.m, most, timer, nullptr, 0, nullptr,
+                    words, matches, ext)) {
+      pair_declined = W;
+      return false;
+    }
+    pair_cnt = owner_mask_counts(c);
+  }
+  timer.start();
+  owner_pair_sum(c, L[j].F + (uint64_t)x * L[j].cap, L[j].F + (uint64_t)y * L[j].cap, n, v.d[0].rp, v.d[0].col,
+                 pair_cnt, acc);
+  timer.stop();
+  return true;
 }
 
 // Factorised count (Sec. 5.4): the attributes at positions j0..m-1 share no
@@ -461,8 +509,8 @@ void run_static(gj_ctx* c, const gj_graph* g, const gj_query* q, int mode, uint6
     std::unique_lock<std::mutex> lk(gm->hash_mu);  // the slot's plan, as below
     Version& slot = gm->ver[gm->cur];
     uint64_t words = 0, matches = 0, ext = 0;
-    if (owner_mask(c, a, v.d[dir].row, v.d[dir].col, v.d[1 - dir].row, v.d[1 - dir].col, v.m, timer, &slot.plan,
-                   slot.gen, gm->ctx, words, matches, ext)) {
+    if (owner_mask(c, a, v.d[dir].row, v.d[dir].col, v.d[1 - dir].row, v.d[1 - dir].col, v.m,
+                   kOwnerMaskMax / 8, timer, &slot.plan, slot.gen, gm->ctx, words, matches, ext)) {
       lk.unlock();
       overflow = matches > cap;
       if (!overflow && matches) {

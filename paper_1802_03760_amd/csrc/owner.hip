@@ -679,6 +679,31 @@ __global__ void __launch_bounds__(kBlock) k_mask_rows(OwnerArgs a, const uint32_
   }
 }
 
+// Frontiers are in lexicographic order, so neighbouring lanes mostly hold one
+// pair: the first of them searches.
+__global__ void __launch_bounds__(kBlock) k_pair_sum(const uint32_t* __restrict__ x, const uint32_t* __restrict__ y,
+                                                     uint64_t n, const uint32_t* __restrict__ rp,
+                                                     const uint32_t* __restrict__ col,
+                                                     const uint32_t* __restrict__ cnt,
+                                                     unsigned long long* __restrict__ acc) {
+  const int lane = lane_id();
+  const uint64_t gs = (uint64_t)gridDim.x * blockDim.x;
+  uint64_t sum = 0;
+  for (uint64_t b = (uint64_t)blockIdx.x * blockDim.x; b < n; b += gs) {  // whole waves take every step
+    const uint64_t p = b + threadIdx.x;
+    const uint32_t u = p < n ? x[p] : 0, v = p < n ? y[p] : 0;
+    const uint32_t pu = __shfl_up(u, 1, 64), pv = __shfl_up(v, 1, 64);
+    const bool head = lane == 0 || pu != u || pv != v;
+    uint32_t t = 0;
+    if (head && p < n) t = cnt[lower_bound_u32(col, rp[u], rp[u + 1], v)];
+    const uint64_t heads = __ballot(head) & (lanemask_lt() | 1ull << lane);
+    t = __shfl(t, 63 - __clzll((long long)heads), 64);
+    if (p < n) sum += t;
+  }
+  sum = block_sum<kBlock>(sum);
+  if (threadIdx.x == 0 && sum) atomicAdd(acc, (unsigned long long)sum);
+}
+
 // ---------------------------------------------------------------- host
 // The tasks of a launch (kept with the version, or planned now) and the
 // counters it starts from: acc (matches, extensions, signed sum, units split
@@ -780,8 +805,8 @@ void owner_count(gj_ctx* c, const OwnerArgs& a, const uint32_t* seed_row, const 
 }
 
 bool owner_mask(gj_ctx* c, const OwnerArgs& a, const uint32_t* seed_row, const uint32_t* seed_col,
-                const uint32_t* t_row, const uint32_t* t_col, uint64_t E, KernelTimer& timer, OwnerPlan* plan,
-                uint64_t gen, gj_ctx* pc, uint64_t& nw, uint64_t& matches, uint64_t& extensions) {
+                const uint32_t* t_row, const uint32_t* t_col, uint64_t E, uint64_t most_words, KernelTimer& timer,
+                OwnerPlan* plan, uint64_t gen, gj_ctx* pc, uint64_t& nw, uint64_t& matches, uint64_t& extensions) {
   nw = matches = extensions = 0;
   if (!E) return true;
   uint32_t* words = (uint32_t*)ws_get(c, "om_words", (E + 1) * sizeof(uint32_t));
@@ -792,7 +817,7 @@ bool owner_mask(gj_ctx* c, const OwnerArgs& a, const uint32_t* seed_row, const u
   k_mask_words<<<ge, kBlock, 0, c->stream>>>(a, seed_row, seed_col, E, words);
   scan_u32_to_u64(c, words, off, E);
   nw = read_u64(c, off + E);
-  if (nw * sizeof(uint64_t) > kOwnerMaskMax) return false;
+  if (nw > most_words) return false;
   scan_u32(c, words, woff, E);
   unsigned long long* mask = (unsigned long long*)ws_get(c, "om_mask", (nw + 1) * sizeof(uint64_t));
   uint32_t* seed_of = (uint32_t*)ws_get(c, "om_seed", (E + 1) * sizeof(uint32_t));
@@ -811,6 +836,14 @@ bool owner_mask(gj_ctx* c, const OwnerArgs& a, const uint32_t* seed_row, const u
   matches = h[0];
   extensions = h[1];
   return true;
+}
+
+const uint32_t* owner_mask_counts(gj_ctx* c) { return (const uint32_t*)ws_get(c, "om_words", 0); }
+
+void owner_pair_sum(gj_ctx* c, const uint32_t* x, const uint32_t* y, uint64_t n, const uint32_t* rp,
+                    const uint32_t* col, const uint32_t* cnt, unsigned long long* acc) {
+  k_pair_sum<<<grid_for(n, kBlock * 4, (unsigned)c->num_cus * 16), kBlock, 0, c->stream>>>(x, y, n, rp, col, cnt, acc);
+  GJ_HIP(hipGetLastError());
 }
 
 void owner_rows(gj_ctx* c, const OwnerArgs& a, const uint32_t* seed_row, const uint32_t* seed_col, uint64_t E,
