@@ -15,16 +15,17 @@
 //
 // The matrix costs one walk of the members' own prefixes, the sum over edges
 // of the hub-side degree (4.4e9 entries at R-MAT-20 undirected), against
-// 5.8e10 candidates of the depth-first evaluation there, and the counts read
-// LDS only.  Counters are the depth-first ones: prefixes are cliques, and
-// extensions sum the least out-degree of a prefix's vertices.
+// 5.8e10 candidates of the depth-first evaluation there; members among the
+// hubs take bit reads instead (k_cb_bits).  The counts read LDS only.  Counters
+// are the depth-first ones: prefixes are cliques, and extensions sum the least
+// out-degree of a prefix's vertices.
 //
-// Measured (MI355X): R-MAT-20 oriented 4-clique 177 -> 22 ms, oriented 5-clique
-// of a 300,007-vertex R-MAT graph 20.3 -> 6.8 ms, directed R-MAT-17 4-clique
-// 90.6 -> 2.4 ms, against a wave per seed edge that probes rows in memory for
+// Measured (MI355X): R-MAT-20 oriented 4-clique 177 -> 7.8 ms, oriented 5-clique
+// of a 300,007-vertex R-MAT graph 20.3 -> 5.5 ms, directed R-MAT-17 4-clique
+// 90.6 -> 1.7 ms, against a wave per seed edge that probes rows in memory for
 // every a2 (clique.hip, still there for inequalities and where a vertex has
-// more than 1,056 neighbours of higher degree).  Bound by the build's hash
-// probes (16 of the 22 ms), then by the counts' LDS reads and popcounts.
+// more than 1,056 neighbours of higher degree).  Bound by the build's probes
+// and bit reads, then by the counts' LDS reads and popcounts.
 #include <algorithm>
 
 #include "gj_internal.h"
@@ -37,6 +38,13 @@ namespace gj {
 enum { kCbMatches, kCbExt2, kCbPre3, kCbExt3, kCbPre4, kCbExt4, kCbAcc };
 constexpr int kCbClasses = 4;
 constexpr uint32_t kCbCap[kCbClasses] = {64, 256, 512, 1056};
+// Edges from which the hubs' adjacency bits are built, where some vertex has
+// more than kCbCap[0] neighbours below it.  Their build is some 40 us: R-MAT-15
+// (3.2e5 edges) 4-clique 795 -> 729 us and 5-clique 1,481 -> 1,487, R-MAT-16
+// 1,008 -> 857 and 1,835 -> 1,853, R-MAT-17 1,628 -> 1,080 and 4,047 -> 3,437;
+// uniform random graphs, whose members have short rows, lose (5.2e5 edges: 367
+// -> 430 us).
+constexpr uint64_t kCbBitsEdges = 500000;
 constexpr uint32_t kCbAsIs = 16384, kCbAsIsDeg = 512;  // vertices and degree up to which ids stay as they are
 
 // extensions[2]: the lesser out-degree of every edge's ends
@@ -77,6 +85,31 @@ __global__ void __launch_bounds__(kBlock) k_cb_classes(HubGraph g, unsigned int*
     __syncthreads();
     if (c >= 0 && c < kCbClasses) lists[(uint64_t)c * g.n + base[c] + at] = (uint32_t)v;
     __syncthreads();
+  }
+}
+
+// Adjacency of the hubs: bit x of row u (kCbTop / 32 words) of bits[s] is set
+// for x in the prefix of u's row in direction s, for u below kCbTop.  null:
+// not built (bits[1] also where no vertex has an in-prefix).  Most members of
+// the larger v are such hubs, and a member's edges to the ones below it are
+// then bit reads, members' pairs of v only, instead of a walk of its whole
+// prefix against v's hash table (oriented R-MAT-20, 4-clique: 22.6 -> 7.8
+// ms, 5-clique at 300,007 vertices 6.9 -> 5.5 ms).
+constexpr uint32_t kCbTop = 32768;
+struct CbBits {
+  const uint32_t* bits[2];
+};
+
+// a wave per hub and direction
+__global__ void __launch_bounds__(kBlock) k_cb_bits(HubGraph g, uint32_t top, uint32_t* __restrict__ b0,
+                                                    uint32_t* __restrict__ b1) {
+  const uint32_t w = blockIdx.x * (kBlock / 64) + wave_id(), u = w >> 1, s = w & 1;
+  uint32_t* b = s ? b1 : b0;
+  if (u >= top || !b) return;
+  const uint32_t lo = g.rp[s][u], n = g.end[s][u] - lo;
+  for (uint32_t i = lane_id(); i < n; i += 64) {
+    const uint32_t x = g.col[s][(uint64_t)lo + i];
+    atomicOr(b + (uint64_t)u * (kCbTop / 32) + (x >> 5), 1u << (x & 31));
   }
 }
 
@@ -122,7 +155,7 @@ __device__ __forceinline__ void cb_insert(CbLds<CAP, SLOTS>& s, uint32_t x, uint
 // Builds v's members and matrix with NT threads (nw waves, this one wave);
 // sync separates their phases.  Returns the number of members.
 template <uint32_t CAP, uint32_t SLOTS, class Sync>
-__device__ __forceinline__ uint32_t cb_build(CbLds<CAP, SLOTS>& s, const HubGraph& g, uint32_t v,
+__device__ __forceinline__ uint32_t cb_build(CbLds<CAP, SLOTS>& s, const HubGraph& g, const CbBits& hb, uint32_t v,
                                              uint32_t tid, uint32_t nt, Sync sync) {
   const uint32_t lane = lane_id(), wave = tid / 64, nw = nt / 64;
   const uint32_t b0 = g.rp[0][v], n0 = g.end[0][v] - b0, b1 = g.rp[1][v], n1 = g.end[1][v] - b1;
@@ -151,15 +184,45 @@ __device__ __forceinline__ uint32_t cb_build(CbLds<CAP, SLOTS>& s, const HubGrap
   sync();
   const uint32_t n = s.n;
   for (uint32_t i = tid; i < n; i += nt) s.deg[i] = g.deg(0, s.id[i]);
-  // the members' prefixes, out- and in-, as rows tagged with member and side
+  // the hubs among the members: 64 / P of them at a time, P lanes of members
+  // each, tested for the members below
+  constexpr uint32_t kStride = CbLds<CAP, SLOTS>::kStride;
+  const uint32_t top = hb.bits[0] ? kCbTop : 0;
+  if (top) {
+    const uint32_t lg = n > 32 ? 6 : n > 16 ? 5 : n > 8 ? 4 : 3, P = 1u << lg;
+    const uint32_t sub = lane & (P - 1), first = lane >> lg;
+    for (uint32_t i0 = wave << (6 - lg); i0 < n; i0 += nw << (6 - lg)) {
+      const uint32_t i = i0 + first, u = i < n ? s.id[i] : ~0u;
+      const uint64_t at = (uint64_t)u * (kCbTop / 32);
+      const uint32_t most = n1 || lg < 6 ? n : i0;  // without in-neighbours the members ascend
+      for (uint32_t j0 = 0; j0 < most; j0 += P) {
+        const uint32_t j = j0 + sub, x = j < n ? s.id[j] : ~0u;
+        const bool below = u < top && x < u;
+        const uint64_t b = __ballot(below && (hb.bits[0][at + (x >> 5)] >> (x & 31) & 1));
+        if (lg == 6) {
+          if (lane < 2 && (uint32_t)(b >> (32 * lane)))
+            atomicOr(&s.mat[((j0 >> 5) + lane) * kStride + i0], (uint32_t)(b >> (32 * lane)));
+        } else if (sub == 0) {
+          const uint32_t mine = (uint32_t)(b >> (first << lg)) & (uint32_t)((1ull << P) - 1);
+          if (mine) atomicOr(&s.mat[i], mine);
+        }
+        if (hb.bits[1] && below && (hb.bits[1][at + (x >> 5)] >> (x & 31) & 1))
+          atomicOr(&s.mat[(i >> 5) * kStride + j], 1u << (i & 31));
+      }
+    }
+  }
+  // the other members' prefixes, out- and in-, as rows tagged with member and
+  // side
   for (uint32_t r0 = wave * 64; r0 < 2 * n; r0 += nw * 64) {
     const uint32_t r = r0 + lane, i = r >> 1, side = r & 1;
     uint32_t p = 0, q = 0;
     if (r < 2 * n) {
       const uint32_t u = s.id[i];
-      const uint32_t* pq = side ? g.pq[1] : g.pq[0];
-      p = pq[u];
-      q = pq[(uint64_t)u + 1] - p;
+      if (u >= top) {
+        const uint32_t* pq = side ? g.pq[1] : g.pq[0];
+        p = pq[u];
+        q = pq[(uint64_t)u + 1] - p;
+      }
     }
     const uint64_t some = __ballot(q != 0), lt = lanemask_lt();
     const uint32_t cn = (uint32_t)__popcll(some);
@@ -170,7 +233,7 @@ __device__ __forceinline__ uint32_t cb_build(CbLds<CAP, SLOTS>& s, const HubGrap
       const uint32_t j = cb_find(s, x);  // ~0 is not found
       if (j == ~0u) return;
       const uint32_t i = tag >> 1, a = tag & 1 ? j : i, b = tag & 1 ? i : j;  // side 0: i -> x, side 1: x -> i
-      atomicOr(&s.mat[(b >> 5) * CbLds<CAP, SLOTS>::kStride + a], 1u << (b & 31));
+      atomicOr(&s.mat[(b >> 5) * kStride + a], 1u << (b & 31));
     });
   }
   sync();
@@ -398,7 +461,7 @@ __device__ __forceinline__ void cb_count(const CbLds<CAP, SLOTS>& s, uint16_t* s
 
 // One v per workgroup (CAP above 64) or per wave.
 template <int Q, uint32_t CAP, uint32_t SLOTS, int NT>
-__global__ void __launch_bounds__(NT) k_cb_cliques(HubGraph g, const uint32_t* __restrict__ list,
+__global__ void __launch_bounds__(NT) k_cb_cliques(HubGraph g, CbBits hb, const uint32_t* __restrict__ list,
                                                    const unsigned int* __restrict__ len,
                                                    unsigned long long* __restrict__ acc) {
   constexpr bool kWave = CAP <= 64;
@@ -422,7 +485,7 @@ __global__ void __launch_bounds__(NT) k_cb_cliques(HubGraph g, const uint32_t* _
   };
   for (uint64_t k = (uint64_t)blockIdx.x * kGroups + grp; k < total; k += (uint64_t)gridDim.x * kGroups) {
     const uint32_t v = (uint32_t)__builtin_amdgcn_readfirstlane((int)list[k]);
-    const uint32_t n = cb_build(s, g, v, tid, kNT, sync), dv = g.deg(0, v);
+    const uint32_t n = cb_build(s, g, hb, v, tid, kNT, sync), dv = g.deg(0, v);
     const uint32_t w = kWave ? 0 : wave, nw = kNT / 64;
     if (g.end[1][v] == g.rp[1][v])
       cb_count<Q, false>(s, sel, n, dv, w, nw, t);
@@ -438,17 +501,17 @@ __global__ void __launch_bounds__(NT) k_cb_cliques(HubGraph g, const uint32_t* _
 
 // most: the greatest number of neighbours a vertex may have below it
 template <int Q>
-static void launch(gj_ctx* c, const HubGraph& g, const uint32_t* lists, const unsigned int* len, uint64_t most,
-                   unsigned long long* acc) {
+static void launch(gj_ctx* c, const HubGraph& g, const CbBits& hb, const uint32_t* lists, const unsigned int* len,
+                   uint64_t most, unsigned long long* acc) {
   const unsigned cus = (unsigned)c->num_cus;
   const uint64_t n = g.n;
   if (most > kCbCap[2])
-    k_cb_cliques<Q, kCbCap[3], 2048, 1024><<<cus, 1024, 0, c->stream>>>(g, lists + 3 * n, len + 3, acc);
+    k_cb_cliques<Q, kCbCap[3], 2048, 1024><<<cus, 1024, 0, c->stream>>>(g, hb, lists + 3 * n, len + 3, acc);
   if (most > kCbCap[1])
-    k_cb_cliques<Q, kCbCap[2], 1024, 512><<<cus * 3, 512, 0, c->stream>>>(g, lists + 2 * n, len + 2, acc);
+    k_cb_cliques<Q, kCbCap[2], 1024, 512><<<cus * 3, 512, 0, c->stream>>>(g, hb, lists + 2 * n, len + 2, acc);
   if (most > kCbCap[0])
-    k_cb_cliques<Q, kCbCap[1], 512, 256><<<cus * 8, 256, 0, c->stream>>>(g, lists + n, len + 1, acc);
-  k_cb_cliques<Q, kCbCap[0], 128, 256><<<cus * 8, 256, 0, c->stream>>>(g, lists, len, acc);
+    k_cb_cliques<Q, kCbCap[1], 512, 256><<<cus * 8, 256, 0, c->stream>>>(g, hb, lists + n, len + 1, acc);
+  k_cb_cliques<Q, kCbCap[0], 128, 256><<<cus * 8, 256, 0, c->stream>>>(g, hb, lists, len, acc);
 }
 
 bool clique_bits_count(gj_ctx* c, const Version& v, uint32_t n, bool by_degree, int q, KernelTimer& timer,
@@ -483,12 +546,27 @@ bool clique_bits_count(gj_ctx* c, const Version& v, uint32_t n, bool by_degree, 
     g = hub_graph(c, v, n, HubOrder::kDegree, row);
     if (!classes()) return false;
   }
+  CbBits hb{};
+  if (v.m >= kCbBitsEdges && most > kCbCap[0]) {
+    // quads of the two directions end to end: does any vertex have an in-prefix?
+    uint32_t h[2];
+    read_u32s(c, {g.pq[1], g.pq[1] + n}, h);
+    const uint32_t top = std::min(n, kCbTop);
+    const uint64_t words = (uint64_t)top * (kCbTop / 32);
+    const int dirs = h[0] == h[1] ? 1 : 2;
+    uint32_t* b = (uint32_t*)ws_get(c, "cb_bits", dirs * words * sizeof(uint32_t));
+    GJ_HIP(hipMemsetAsync(b, 0, dirs * words * sizeof(uint32_t), c->stream));
+    hb.bits[0] = b;
+    hb.bits[1] = dirs == 2 ? b + words : nullptr;
+    k_cb_bits<<<(2 * top + kBlock / 64 - 1) / (kBlock / 64), kBlock, 0, c->stream>>>(g, top, b,
+                                                                                    dirs == 2 ? b + words : nullptr);
+  }
   timer.start();
   k_cb_ext2<<<grid_for(v.m, kBlock * 4, cus * 16), kBlock, 0, c->stream>>>(g, row, v.m, acc);
   if (q == 4)
-    launch<4>(c, g, lists, len, most, acc);
+    launch<4>(c, g, hb, lists, len, most, acc);
   else
-    launch<5>(c, g, lists, len, most, acc);
+    launch<5>(c, g, hb, lists, len, most, acc);
   timer.stop();
   GJ_HIP(hipGetLastError());
   unsigned long long h[kCbAcc];

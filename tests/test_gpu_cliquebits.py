@@ -54,3 +54,16 @@ def test_complete():
     n = 40
     s, d = np.nonzero(~np.eye(n, dtype=bool))
     check(n, s.astype(np.uint32), d.astype(np.uint32))
+
+
+@pytest.mark.parametrize("oriented", [False, True])
+def test_hub_bits(oriented):
+    """Above 500,000 edges members among the 32,768 first vertices are tested by
+    bits: 500 groups of 80 vertices, and one of 120, on either side of that."""
+    rng = np.random.default_rng(5)
+    n, at = 40000, rng.permutation(40000).astype(np.uint32)
+    base = np.repeat(80 * np.arange(500), 1600)
+    s = np.concatenate([at[base + rng.integers(0, 80, len(base))], at[rng.integers(0, 120, 8000)]])
+    d = np.concatenate([at[base + rng.integers(0, 80, len(base))], at[rng.integers(0, 120, 8000)]])
+    assert len(np.unique(s.astype(np.uint64) << np.uint64(32) | d)) > 600000
+    check(n, s, d, **({"degree_order": True} if oriented else {}))
