@@ -27,11 +27,11 @@
 // v is nearly always a hub, so a counter array over [0, 32768) in LDS takes
 // 99% of them.  A (or O) and B (or I) share one word per v.
 //
-// Measured (MI355X): R-MAT-18 diamond 128.3 -> 3.5 ms, 4-cycle of a
+// Measured (MI355X): R-MAT-18 diamond 128.3 -> 3.4 ms, 4-cycle of a
 // 600,011-vertex R-MAT graph (8.4e6 edges) 404 -> 3.8 ms, against one walk of
 // all 2-paths of an a0 with atomics on a dense array of counters in HBM, which
 // were its bound (1.8e10 atomics/s).  Now the walks (k_hub_dense, k_hub_small,
-// k_hub_wave) are 70% of the time and issue-bound, the renaming's sorts 15%.
+// k_hub_wave) are 70% of the time and issue-bound, the renaming's sorts 12%.
 #include <algorithm>
 
 #include "gj_internal.h"
