@@ -102,29 +102,26 @@ __global__ void k_split_keys(const uint64_t* __restrict__ keys, uint64_t m, uint
   }
 }
 
-// rp[v] = first entry of row v in a row-sorted entry list (rp[n] = m): entry
-// e starts the rows after its predecessor's up to its own (and entry m those
-// up to n).  Runs of empty rows longer than a few are filled by the whole
-// wave.  (A search per vertex: 4.2e6 vertices, 163 -> 142 us.)
-__global__ void __launch_bounds__(kBlock) k_rowptr(const uint32_t* __restrict__ row, uint64_t m, uint32_t n,
-                                                   uint32_t* __restrict__ rp) {
-  constexpr uint64_t kAlone = 8;
-  const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-  for (uint64_t b = (uint64_t)blockIdx.x * blockDim.x; b <= m; b += stride) {  // whole waves take every step
-    const uint64_t e = b + threadIdx.x;
-    uint64_t lo = 0, hi = 0;  // rows [lo, hi) start at e
-    if (e <= m) {
-      lo = e ? (uint64_t)row[e - 1] + 1 : 0;
-      hi = e < m ? (uint64_t)row[e] + 1 : (uint64_t)n + 1;
+// rp[v] = first entry of row v in a row-sorted entry list (rp[n] = m), by a
+// search per vertex: bound by its chain of some 26 loads, 163 us a direction
+// at 4.2e6 vertices and 6.7e7 entries, and the same whatever the rows.  (An
+// entry that writes the starts of the rows it ends takes 142 us there, but
+// leaves a long run of empty rows to one wave: 4.2e6 vertices without edges
+// 2 ms a direction against 15 us.)
+__global__ void k_rowptr(const uint32_t* __restrict__ row, uint64_t m, uint32_t n, uint32_t* __restrict__ rp) {
+  uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
+  for (uint64_t v = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; v <= n; v += stride) {
+    uint64_t lo = 0, len = m;
+    while (len > 0) {
+      uint64_t half = len >> 1;
+      if (row[lo + half] < v) {
+        lo += half + 1;
+        len -= half + 1;
+      } else {
+        len = half;
+      }
     }
-    const bool big = hi > lo + kAlone;
-    if (!big)
-      for (; lo < hi; ++lo) rp[lo] = (uint32_t)e;
-    for (uint64_t left = __ballot(big); left; left &= left - 1) {
-      const int src = __ffsll((unsigned long long)left) - 1;
-      const uint64_t l = shfl_u64(lo, src), h = shfl_u64(hi, src), x = shfl_u64(e, src);
-      for (uint64_t v = l + lane_id(); v < h; v += 64) rp[v] = (uint32_t)x;
-    }
+    rp[v] = (uint32_t)lo;
   }
 }
 
@@ -188,7 +185,8 @@ void version_finish(gj_ctx* c, Version& v, uint32_t n, bool from_update) {
   if (!from_update) {
     GJ_HIP(hipMemsetAsync(mx, 0, 2 * sizeof(uint32_t), c->stream));
     for (int d = 0; d < 2; ++d) {
-      k_rowptr<<<grid_for(v.m + 1, kBlock, 1u << 16), kBlock, 0, c->stream>>>(v.d[d].row, v.m, n, v.d[d].rp);
+      k_rowptr<<<grid_for((uint64_t)n + 1, kBlock, 1u << 16), kBlock, 0, c->stream>>>(v.d[d].row, v.m, n,
+                                                                                        v.d[d].rp);
       k_maxdeg<<<grid_for(n, kBlock * 16, 1024), kBlock, 0, c->stream>>>(v.d[d].rp, n, mx + d);
     }
     GJ_HIP(hipGetLastError());
@@ -318,7 +316,7 @@ void graph_build_sym(gj_ctx* c, gj_graph* g, const uint32_t* d_src, const uint32
     uint64_t* vk2 = (uint64_t*)alloc((uint64_t)n * sizeof(uint64_t));
     uint32_t* new_of_old = (uint32_t*)alloc((uint64_t)n * sizeof(uint32_t));
     unsigned gn = grid_for((uint64_t)n + 1, kBlock, 1u << 16);
-    k_rowptr<<<grid_for(ms + 1, kBlock, 1u << 16), kBlock, 0, c->stream>>>(srow, ms, n, rp);
+    k_rowptr<<<gn, kBlock, 0, c->stream>>>(srow, ms, n, rp);
     k_degree_keys<<<gn, kBlock, 0, c->stream>>>(rp, n, vk);
     uint64_t* vs = sort_u64(c, vk, vk2, n, 0, bits);  // stable: equal degrees by id
     g->old_of_new = (uint32_t*)dev_alloc(c, (uint64_t)n * sizeof(uint32_t));
