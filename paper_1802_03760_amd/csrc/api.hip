@@ -85,6 +85,18 @@ void* ws_get(gj_ctx* c, const std::string& name, size_t bytes) {
   return b.p;
 }
 
+void ws_drop(gj_ctx* c, const std::string& prefix) {
+  bool synced = false;
+  for (auto it = c->ws.lower_bound(prefix); it != c->ws.end() && it->first.compare(0, prefix.size(), prefix) == 0;) {
+    if (it->second.p) {
+      if (!synced) GJ_HIP(hipStreamSynchronize(c->stream));
+      synced = true;
+      dev_free(c, it->second.p);
+    }
+    it = c->ws.erase(it);
+  }
+}
+
 void read_bytes(gj_ctx* c, void* host, const void* dptr, size_t bytes) {
   if (bytes <= 4096) {
     GJ_HIP(hipMemcpyAsync(c->pinned, dptr, bytes, hipMemcpyDeviceToHost, c->stream));

@@ -370,19 +370,25 @@ void Runner::stage(int j, uint64_t n) {
 // ends' sets.  They are counted once per edge, by the owner-grouped pass, and
 // summed over the prefixes, when the stage has at least kPairGain times the
 // candidates that takes (a word of 64 per edge and part of its smaller set).
+// Adding up the edges' words takes a pass over all of them, so a batch that
+// would not pay at kPairWords words an edge does without (the pass is then at
+// most a fortieth of the batch: R-MAT-20 0.22 ms, of a house slice's 4.49 at
+// half that line).  Nor does j = 2 look, where the prefixes are the edges
+// themselves: triangles of a thousandth of R-MAT-20's edges 337 us, 532 with.
 // House: 4.55 ms of run kernels (a shared set rebuilt for every a1) -> 0.15 ms
 // at R-MAT with 4,099 vertices, the whole query 76.4 -> 10.0 ms at 16,379;
 // uniform random graphs to 9.6e6 edges stay below the line and as they were.
-constexpr uint64_t kPairGain = 2;
+constexpr uint64_t kPairGain = 2, kPairWords = 2;
 
 bool Runner::by_pair(int j, uint64_t n, uint64_t W) {
   const std::vector<BindH>& b = P.bind[j];
-  if (collect || weighted || V.delta_atom >= 0 || !V.graph || c->arena.on || !c->run_stage || c->strategy == 1 ||
+  if (j == 2 || collect || weighted || V.delta_atom >= 0 || !V.graph || c->arena.on || !c->run_stage || c->strategy == 1 ||
       W < c->run_stage_min || P.above[j] || P.below[j] || b.size() != 2 || b[0].col2 >= 0 || b[1].col2 >= 0 ||
       b[0].col == b[1].col)
     return false;
   const Version& v = *V.old_v;
-  if (v.pmap[0] || v.pmap[1] || W <= pair_declined) return false;
+  if (v.pmap[0] || v.pmap[1]) return false;
+  if (!pair_cnt && (W <= pair_declined || W / (64 * kPairGain) < kPairWords * v.m)) return false;
   int x = -1, y = -1;  // columns of an edge x -> y among the two
   for (const auto& e : P.edges)
     if ((e.first == b[0].col && e.second == b[1].col) || (e.first == b[1].col && e.second == b[0].col)) {
@@ -396,9 +402,13 @@ bool Runner::by_pair(int j, uint64_t n, uint64_t W) {
                 v.d[0].rp,     v.d[0].col,     v.d[1].rp,      v.d[1].col,      V.graph->n};
     uint64_t words = 0, matches = 0, ext = 0;
     const uint64_t most = std::min(kOwnerMaskMax / 8, W / (64 * kPairGain));
-    if (!owner_mask(c, a, v.d[0].row, v.d[0].col, v.d[1].row, v.d[1].col, v.m, most, timer, nullptr, 0, nullptr,
-                    words, matches, ext)) {
-      pair_declined = W;
+    bool taken = false;
+    const bool fits = ws_fits(c, {"om_"}, [&] {
+      taken = owner_mask(c, a, v.d[0].row, v.d[0].col, v.d[1].row, v.d[1].col, v.m, most, timer, nullptr, 0, nullptr,
+                         words, matches, ext);
+    });
+    if (!taken) {
+      pair_declined = fits ? W : ~0ull;
       return false;
     }
     pair_cnt = owner_mask_counts(c);

@@ -304,6 +304,23 @@ class KernelTimer {
 // workspace buffers up to this size are retired rather than freed when they grow
 constexpr size_t kWsRetireMax = 256ull << 20;
 void* ws_get(gj_ctx* c, const std::string& name, size_t bytes);
+// Gives back the workspace buffers whose names start with `prefix`, once the
+// stream is done with them.
+void ws_drop(gj_ctx* c, const std::string& prefix);
+// f(), which takes its workspace under the given name prefixes.  False, and
+// that workspace given back, when device memory does not hold it: the caller
+// then takes a path that needs less.
+template <class F>
+bool ws_fits(gj_ctx* c, std::initializer_list<const char*> prefixes, F&& f) {
+  try {
+    f();
+    return true;
+  } catch (const Error& e) {
+    if (e.code != GJ_ENOMEM) throw;
+  }
+  for (const char* p : prefixes) ws_drop(c, p);
+  return false;
+}
 // Device memory through the context's allocator (hipMalloc / hipFree without
 // one).  dev_alloc throws GJ_ENOMEM on failure; dev_free(c, null) is a no-op.
 void dev_free(gj_ctx* c, void* p);

@@ -810,7 +810,6 @@ bool owner_mask(gj_ctx* c, const OwnerArgs& a, const uint32_t* seed_row, const u
   nw = matches = extensions = 0;
   if (!E) return true;
   uint32_t* words = (uint32_t*)ws_get(c, "om_words", (E + 1) * sizeof(uint32_t));
-  uint32_t* woff = (uint32_t*)ws_get(c, "om_woff", (E + 1) * sizeof(uint32_t));
   uint64_t* off = (uint64_t*)ws_get(c, "om_off", (E + 1) * sizeof(uint64_t));
   const unsigned ge = grid_for(E, kBlock * 4, 1u << 14);
   // 64-bit offsets first (in the row offsets' buffer): the words may exceed 32 bits
@@ -818,6 +817,7 @@ bool owner_mask(gj_ctx* c, const OwnerArgs& a, const uint32_t* seed_row, const u
   scan_u32_to_u64(c, words, off, E);
   nw = read_u64(c, off + E);
   if (nw > most_words) return false;
+  uint32_t* woff = (uint32_t*)ws_get(c, "om_woff", (E + 1) * sizeof(uint32_t));
   scan_u32(c, words, woff, E);
   unsigned long long* mask = (unsigned long long*)ws_get(c, "om_mask", (nw + 1) * sizeof(uint64_t));
   uint32_t* seed_of = (uint32_t*)ws_get(c, "om_seed", (E + 1) * sizeof(uint32_t));

@@ -7,6 +7,10 @@ import pytest
 
 import torch
 
+import oracle
+import synth
+from tests import queries as Q
+
 pytestmark = pytest.mark.gpu
 
 
@@ -42,3 +46,97 @@ def test_empty_rows(edges):
     v = np.concatenate([np.arange(0, 3000), np.arange(n - 3000, n + 1), rng.integers(0, n, 3000)])
     assert np.array_equal(rp[v], np.searchsorted(pairs // n, v))
     assert best < 12e-3, best
+
+
+class Bounded:
+    """hipMalloc / hipFree as a context's allocator: counts the bytes held, and
+    refuses a single allocation above `most` once that is set, or the one
+    numbered `fail_at`."""
+
+    def __new__(cls, gj):
+        import ctypes
+        hip = ctypes.CDLL("libamdhip64.so")
+
+        class A(gj.DeviceAllocator):
+            live, most, refused, n, fail_at = {}, None, 0, 0, None
+
+            def alloc(self, nbytes, stream):
+                self.n += 1
+                if (self.most is not None and nbytes > self.most) or self.n == self.fail_at:
+                    self.refused += 1
+                    return 0
+                p = ctypes.c_void_p()
+                if hip.hipMalloc(ctypes.byref(p), ctypes.c_size_t(nbytes)) != 0:
+                    return 0
+                self.live[p.value] = nbytes
+                return p.value
+
+            def free(self, ptr, stream):
+                del self.live[ptr]
+                hip.hipFree(ctypes.c_void_p(ptr))
+
+            @property
+            def held(self):
+                return sum(self.live.values())
+
+        a = A()
+        a.live = {}
+        return a
+
+
+def same(got, want, tag=""):
+    for k in ("matches", "prefixes", "extensions"):
+        assert got[k] == want[k], (tag, k, got[k], want[k])
+
+
+@pytest.mark.parametrize("query", [Q.TRIANGLE, Q.CYCLIC_TRIANGLE, Q.HOUSE])
+def test_slice_workspace(query):
+    """A slice's count takes no workspace in the size of the whole graph, only
+    its frontiers (and what a membership index takes, which is off here)."""
+    import paper_1802_03760_amd as gj
+    s, d = synth.rmat_draws(16, 12, seed=1)
+    A = Bounded(gj)
+    ctx = gj.Context(0, allocator=A)
+    for k, v in (("run_stage_min", 0), ("hash_index", 0), ("frontier_cap", 1 << 14), ("seed_chunk", 1 << 12)):
+        ctx.set_option(k, v)
+    G = gj.Graph(ctx, s, d, 1 << 16)
+    E = G.info()["edges"]
+    before = A.held
+    hi = 4000 if query[0] == 3 else 3
+    got = gj.count(ctx, G, gj.Query(ctx, *query), 0, hi)
+    same(got, oracle.run(oracle.Graph(1 << 16, s, d), query, seed_lo=0, seed_hi=hi, threads=8))
+    assert A.held - before < 4 * E, (A.held - before, E)
+
+
+def test_edge_counts_without_room():
+    """The house's last stage counted per edge: an allocation that fails there
+    leaves the stage to the kernels it replaces."""
+    import paper_1802_03760_amd as gj
+    s, d = synth.rmat_draws(9, 12, seed=1)
+    want = oracle.run(oracle.Graph(512, s, d), Q.HOUSE, threads=8)
+
+    def run(fail_at):
+        A = Bounded(gj)
+        ctx = gj.Context(0, allocator=A)
+        ctx.set_option("run_stage_min", 0)
+        G = gj.Graph(ctx, s, d, 512)
+        q = gj.Query(ctx, *Q.HOUSE)
+        built = A.n
+        A.fail_at = built + fail_at if fail_at else None
+        try:
+            got = gj.count(ctx, G, q)
+        except gj.GJError as e:
+            assert e.status == gj.GJ_ENOMEM
+            got = None
+        last = A.n - built
+        if got:
+            same(got, want, fail_at)
+        same(gj.count(ctx, G, q), want, fail_at)
+        q.close(), G.close(), ctx.close()
+        assert not A.live
+        return got is not None, last
+
+    _, last = run(0)
+    through = [run(i)[0] for i in range(1, last + 1)]
+    # its workspace: counts, row offsets, word offsets, mask, transposed seeds
+    assert sum(through) >= 5, through
