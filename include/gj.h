@@ -211,7 +211,11 @@ const char* gj_last_error(const gj_ctx* ctx);
  *   "run_stage_min" run_stage: least count-minimised candidates of a stage
  *                   for it to take the run kernels (default 2^22, >= 0;
  *                   a smaller stage takes the per-candidate kernel, which
- *                   finishes it in about the time planning the runs takes)
+ *                   finishes it in about the time planning the runs takes).
+ *                   0 also has whole listings of three-attribute queries go
+ *                   through the owner-grouped kernel whatever their size,
+ *                   which by default takes those of 65,536 edges and 786,432
+ *                   candidates, three an edge, or more
  *   "run_min_tasks" run_stage: a stage whose staged runs make fewer tasks
  *                   than this (default 256, >= 0) is left whole to the
  *                   per-candidate kernel (a workgroup works through a task

@@ -504,6 +504,7 @@ void apply_updates(gj_ctx* c, gj_graph* g, const uint32_t* src, const uint32_t* 
     ++nv.gen;  // written (as version_finish marks a slot)
     nv.max_deg[0] = h3[1];
     nv.max_deg[1] = h3[2];
+    nv.two[0] = nv.two[1] = nv.two[2] = ~0ull;
   }
   const Version& ov = patched ? lsm_old : cur_view;
   const Version& nv = patched ? lsm_new : g->ver[target];

@@ -404,8 +404,8 @@ bool Runner::by_pair(int j, uint64_t n, uint64_t W) {
     const uint64_t most = std::min(kOwnerMaskMax / 8, W / (64 * kPairGain));
     bool taken = false;
     const bool fits = ws_fits(c, {"om_"}, [&] {
-      taken = owner_mask(c, a, v.d[0].row, v.d[0].col, v.d[1].row, v.d[1].col, v.m, most, timer, nullptr, 0, nullptr,
-                         words, matches, ext);
+      taken = owner_mask(c, a, v.d[0].row, v.d[0].col, v.d[1].row, v.d[1].col, v.m, 0, most, timer, nullptr, 0,
+                         nullptr, words, matches, ext);
     });
     if (!taken) {
       pair_declined = fits ? W : ~0ull;
@@ -487,6 +487,74 @@ static bool identity(const std::vector<int>& o) {
   return true;
 }
 
+// The sets of the owner-grouped kernel, listed, for the graph's current version
+// v.  False where they have too few candidates, the mask is too large, or
+// device memory does not hold it.
+//
+// The candidates W = sum of min(|LA|, |LB|) decide: the mask's passes cost some
+// 60 us and 150 us a million edges whatever W, the per-candidate kernels 25 us
+// a million candidates.  Uniform graphs, per-candidate against listed: W = 1.6
+// m, m = 1.3e5 140 us / 165 us, m = 8.4e6 1.10 / 1.59 ms; W = 6.9 m, m = 1.3e5
+// 188 / 167 us, m = 8.4e6 2.40 / 1.53 ms; R-MAT-13 of 85,000 edges, W = 3.8e6,
+// 300 / 260 us; below kListEdges the look itself costs what is gained.  A bound on W, the 2-paths through the vertices of either side
+// of the seed edges, is known without looking at the edges (a one-way graph of
+// 1e6 edges has none: 98 us, 262 with the passes); the first pass adds W up.
+constexpr uint64_t kListMin = 3ull << 18, kListEdge = 3, kListEdges = 1ull << 16;
+
+static uint64_t two_paths(const Version& v, int a, int b) { return v.two[a == b ? a : 2]; }
+
+static bool list_whole(gj_ctx* c, const gj_graph* g, const PlanH& P, const Version& v, uint32_t* out, uint64_t cap,
+                       int out_on_device, gj_stats* st, bool& overflow) {
+  const int dir = P.seed_fwd ? 0 : 1;
+  const BindH& A = P.bind[2][0].col == 0 ? P.bind[2][0] : P.bind[2][1];
+  const BindH& B = P.bind[2][0].col == 0 ? P.bind[2][1] : P.bind[2][0];
+  OwnerArgs a{v.d[A.dir].rp, v.d[A.dir].col, v.d[B.dir].rp, v.d[B.dir].col,
+              v.d[dir].rp,   v.d[dir].col,   v.d[1 - dir].rp, v.d[1 - dir].col, g->n};
+  const uint64_t least = c->run_stage_min ? std::max(kListMin, kListEdge * v.m) : 0;
+  if (least && v.m < kListEdges) return false;
+  // W is at most the sum over seed edges of either set
+  if (std::min(two_paths(v, dir, A.dir), two_paths(v, 1 - dir, B.dir)) < least) return false;
+  bool taken = false;
+  const bool fits = ws_fits(c, {"om_"}, [&] {
+    KernelTimer timer(c);
+    gj_graph* gm = const_cast<gj_graph*>(g);
+    std::unique_lock<std::mutex> lk(gm->hash_mu);  // the slot's plan, as for the count
+    Version& slot = gm->ver[gm->cur];
+    uint64_t words = 0, matches = 0, ext = 0;
+    taken = owner_mask(c, a, v.d[dir].row, v.d[dir].col, v.d[1 - dir].row, v.d[1 - dir].col, v.m,
+                       least, kOwnerMaskMax / 8, timer, &slot.plan, slot.gen, gm->ctx, words, matches, ext);
+    if (!taken) return;
+    lk.unlock();
+    overflow = matches > cap;
+    if (!overflow && matches) {
+      DevMem own;
+      uint32_t* rows = out;
+      if (!out_on_device) {
+        own = DevMem(c, matches * P.m * sizeof(uint32_t));
+        rows = own.as<uint32_t>();
+      }
+      RowMap map{};
+      map.m = P.m;
+      for (int k = 0; k < P.m; ++k) map.attr[k] = P.order[k];
+      timer.start();
+      owner_rows(c, a, v.d[dir].row, v.d[dir].col, v.m, words, map, rows);
+      timer.stop();
+      if (matches > 1 && !identity(P.order)) sort_rows(c, rows, nullptr, matches, P.m, g->n);
+      if (!out_on_device)
+        GJ_HIP(hipMemcpyAsync(out, rows, matches * P.m * sizeof(uint32_t), hipMemcpyDeviceToHost, c->stream));
+      GJ_HIP(hipStreamSynchronize(c->stream));
+    }
+    gj_stats s{};
+    s.prefixes[2] = v.m;
+    s.extensions[2] = ext;
+    s.matches = s.prefixes[3] = matches;
+    s.kernel_ms = timer.total_ms();
+    s.kernel_launches = timer.launches();
+    *st = s;
+  });
+  return fits && taken;
+}
+
 void run_static(gj_ctx* c, const gj_graph* g, const gj_query* q, int mode, uint64_t lo, uint64_t hi,
                 uint32_t* out, uint64_t cap, int out_on_device, gj_stats* st, bool& overflow, const Version* ver) {
   PlanH P = make_plan(q, q->order, -1);
@@ -506,51 +574,7 @@ void run_static(gj_ctx* c, const gj_graph* g, const gj_query* q, int mode, uint6
   // edges whose last attribute is bound by one atom on each seed attribute.
   const bool owner = c->strategy != 1 && P.m == 3 && P.filters.empty() && !P.has_ineq() && !P.ntri && lo == 0 &&
                      hi == v.m && P.bind[2].size() == 2 && P.bind[2][0].col != P.bind[2][1].col;
-  // The same sets, listed; below 100,000 edges the per-candidate kernels' fewer
-  // launches win (R-MAT triangles: 47,000 edges 219 us against 237 us,
-  // 180,000 edges 448 against 331).
-  if (owner && collect && !ver && v.m >= 100000) {
-    const BindH& A = P.bind[2][0].col == 0 ? P.bind[2][0] : P.bind[2][1];
-    const BindH& B = P.bind[2][0].col == 0 ? P.bind[2][1] : P.bind[2][0];
-    OwnerArgs a{v.d[A.dir].rp, v.d[A.dir].col, v.d[B.dir].rp, v.d[B.dir].col,
-                v.d[dir].rp,   v.d[dir].col,   v.d[1 - dir].rp, v.d[1 - dir].col, g->n};
-    KernelTimer timer(c);
-    gj_graph* gm = const_cast<gj_graph*>(g);
-    std::unique_lock<std::mutex> lk(gm->hash_mu);  // the slot's plan, as below
-    Version& slot = gm->ver[gm->cur];
-    uint64_t words = 0, matches = 0, ext = 0;
-    if (owner_mask(c, a, v.d[dir].row, v.d[dir].col, v.d[1 - dir].row, v.d[1 - dir].col, v.m,
-                   kOwnerMaskMax / 8, timer, &slot.plan, slot.gen, gm->ctx, words, matches, ext)) {
-      lk.unlock();
-      overflow = matches > cap;
-      if (!overflow && matches) {
-        DevMem own;
-        uint32_t* rows = out;
-        if (!out_on_device) {
-          own = DevMem(c, matches * P.m * sizeof(uint32_t));
-          rows = own.as<uint32_t>();
-        }
-        RowMap map{};
-        map.m = P.m;
-        for (int k = 0; k < P.m; ++k) map.attr[k] = P.order[k];
-        timer.start();
-        owner_rows(c, a, v.d[dir].row, v.d[dir].col, v.m, words, map, rows);
-        timer.stop();
-        if (matches > 1 && !identity(P.order)) sort_rows(c, rows, nullptr, matches, P.m, g->n);
-        if (!out_on_device)
-          GJ_HIP(hipMemcpyAsync(out, rows, matches * P.m * sizeof(uint32_t), hipMemcpyDeviceToHost, c->stream));
-        GJ_HIP(hipStreamSynchronize(c->stream));
-      }
-      gj_stats s{};
-      s.prefixes[2] = v.m;
-      s.extensions[2] = ext;
-      s.matches = s.prefixes[3] = matches;
-      s.kernel_ms = timer.total_ms();
-      s.kernel_launches = timer.launches();
-      *st = s;
-      return;
-    }
-  }
+  if (owner && collect && !ver && list_whole(c, g, P, v, out, cap, out_on_device, st, overflow)) return;
   if (owner && !collect) {
     const BindH& A = P.bind[2][0].col == 0 ? P.bind[2][0] : P.bind[2][1];
     const BindH& B = P.bind[2][0].col == 0 ? P.bind[2][1] : P.bind[2][0];

@@ -134,6 +134,10 @@ struct Version {
   CsrDir d[2];  // 0 forward, 1 reverse
   uint64_t m = 0, cap = 0;
   uint32_t max_deg[2] = {0, 0};
+  // sums over the vertices of out^2, in^2 and out x in (degrees), as known from
+  // a build or a compaction; ~0 after an update.  They bound the work of a
+  // count or listing before it starts; results never depend on them.
+  uint64_t two[3] = {~0ull, ~0ull, ~0ull};
   // contents generation, advanced whenever the slot is written; the index
   // h is valid while hash_gen == gen
   uint64_t gen = 0;
@@ -502,10 +506,9 @@ void sort_rows(gj_ctx* c, uint32_t* rows, int8_t* signs, uint64_t nrows, int m, 
 uint64_t consolidate_rows(gj_ctx* c, const uint32_t* rows, const int8_t* signs, uint64_t nrows, int m,
                           uint32_t* out_rows, int8_t* out_signs, uint64_t cap, int64_t* sum);
 int bits_for(uint32_t n);
-// Row pointers and largest degrees of both directions: computed here from the
-// rows, or (from_update) already written by the update, the degrees into the
-// "maxdeg" workspace.  Reads the degrees back to the host.
-void version_finish(gj_ctx* c, Version& v, uint32_t n, bool from_update);
+// Row pointers, largest degrees and degree sums of both directions, computed
+// from the rows.
+void version_finish(gj_ctx* c, Version& v, uint32_t n);
 
 // api.hip: counts of nreq requests on version ver (null: current), fused
 void count_batch(gj_ctx* c, const gj_graph* g, uint32_t nreq, const gj_query* const* qs, const uint64_t* seed_lo,

@@ -1,6 +1,8 @@
 // Forward and reverse CSR indexes of the edge relation (Sec. 4.1: one forward
 // and one reverse index serve every atom).  Built by sorting (src, dst) keys,
 // dropping repeats and self-loops, and deriving row pointers.
+#include <algorithm>
+
 #include "gj_internal.h"
 #include "prim.h"
 
@@ -125,21 +127,47 @@ __global__ void k_rowptr(const uint32_t* __restrict__ row, uint64_t m, uint32_t 
   }
 }
 
-__global__ void __launch_bounds__(kBlock) k_maxdeg(const uint32_t* __restrict__ rp, uint32_t n,
-                                                   uint32_t* __restrict__ out) {
-  __shared__ uint32_t wbest[kBlock / 64];
-  uint32_t best = 0;
+// Largest degrees of both directions, and the sums over the vertices of out^2,
+// in^2 and out x in: a few atomics per workgroup, into one of kDegreeSlots
+// lines (a thousand workgroups' on one address are some 25 us), which the
+// host adds up.
+constexpr int kDegreeSlots = 32;
+struct alignas(64) DegreeStats {
+  uint32_t most[2];
+  unsigned long long two[3];
+};
+
+__global__ void __launch_bounds__(kBlock) k_degrees(const uint32_t* __restrict__ rp0,
+                                                    const uint32_t* __restrict__ rp1, uint32_t n,
+                                                    DegreeStats* __restrict__ out) {
+  __shared__ uint32_t wbest[2][kBlock / 64];
+  out += blockIdx.x % kDegreeSlots;
+  uint32_t best[2] = {0, 0};
+  uint64_t two[3] = {0, 0, 0};
   uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
   for (uint64_t v = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n; v += stride) {
-    uint32_t d = rp[v + 1] - rp[v];
-    best = d > best ? d : best;
+    const uint32_t d0 = rp0[v + 1] - rp0[v], d1 = rp1[v + 1] - rp1[v];
+    best[0] = d0 > best[0] ? d0 : best[0];
+    best[1] = d1 > best[1] ? d1 : best[1];
+    two[0] += (uint64_t)d0 * d0;
+    two[1] += (uint64_t)d1 * d1;
+    two[2] += (uint64_t)d0 * d1;
   }
-  best = wave_max(best);
-  if (lane_id() == 0) wbest[wave_id()] = best;
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    const uint64_t t = block_sum<kBlock>(two[i]);
+    if (threadIdx.x == 0 && t) atomicAdd(&out->two[i], (unsigned long long)t);
+  }
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    best[i] = wave_max(best[i]);
+    if (lane_id() == 0) wbest[i][wave_id()] = best[i];
+  }
   __syncthreads();
-  if (threadIdx.x == 0) {
-    for (int w = 1; w < kBlock / 64; ++w) best = wbest[w] > best ? wbest[w] : best;
-    atomicMax(out, best);  // one atomic per workgroup
+  if (threadIdx.x < 2) {
+    uint32_t b = 0;
+    for (int w = 0; w < kBlock / 64; ++w) b = wbest[threadIdx.x][w] > b ? wbest[threadIdx.x][w] : b;
+    if (b) atomicMax(&out->most[threadIdx.x], b);
   }
 }
 
@@ -179,22 +207,22 @@ int bits_for(uint32_t n) {
   return b;
 }
 
-void version_finish(gj_ctx* c, Version& v, uint32_t n, bool from_update) {
+void version_finish(gj_ctx* c, Version& v, uint32_t n) {
   ++v.gen;
-  uint32_t* mx = (uint32_t*)ws_get(c, "maxdeg", 2 * sizeof(uint32_t));
-  if (!from_update) {
-    GJ_HIP(hipMemsetAsync(mx, 0, 2 * sizeof(uint32_t), c->stream));
-    for (int d = 0; d < 2; ++d) {
-      k_rowptr<<<grid_for((uint64_t)n + 1, kBlock, 1u << 16), kBlock, 0, c->stream>>>(v.d[d].row, v.m, n,
-                                                                                        v.d[d].rp);
-      k_maxdeg<<<grid_for(n, kBlock * 16, 1024), kBlock, 0, c->stream>>>(v.d[d].rp, n, mx + d);
-    }
-    GJ_HIP(hipGetLastError());
+  DegreeStats h[kDegreeSlots];
+  DegreeStats* stats = (DegreeStats*)ws_get(c, "degrees", sizeof(h));
+  GJ_HIP(hipMemsetAsync(stats, 0, sizeof(h), c->stream));
+  for (int d = 0; d < 2; ++d)
+    k_rowptr<<<grid_for((uint64_t)n + 1, kBlock, 1u << 16), kBlock, 0, c->stream>>>(v.d[d].row, v.m, n, v.d[d].rp);
+  k_degrees<<<grid_for(n, kBlock * 16, 1024), kBlock, 0, c->stream>>>(v.d[0].rp, v.d[1].rp, n, stats);
+  GJ_HIP(hipGetLastError());
+  read_bytes(c, h, stats, sizeof(h));
+  v.max_deg[0] = v.max_deg[1] = 0;
+  v.two[0] = v.two[1] = v.two[2] = 0;
+  for (const DegreeStats& x : h) {
+    for (int d = 0; d < 2; ++d) v.max_deg[d] = std::max(v.max_deg[d], x.most[d]);
+    for (int i = 0; i < 3; ++i) v.two[i] += x.two[i];
   }
-  uint32_t h[2];
-  read_bytes(c, h, mx, sizeof(h));
-  v.max_deg[0] = h[0];
-  v.max_deg[1] = h[1];
 }
 
 void graph_build(gj_ctx* c, gj_graph* g, const uint32_t* d_src, const uint32_t* d_dst, uint64_t m) {
@@ -226,7 +254,7 @@ void graph_build(gj_ctx* c, gj_graph* g, const uint32_t* d_src, const uint32_t* 
   uint64_t* rsorted = sort_u64(c, other, other_alt, mu, 0, bits);
   if (mu) k_split_keys<<<grid_for(mu, kBlock, 1u << 16), kBlock, 0, c->stream>>>(rsorted, mu, v.d[1].row, v.d[1].col);
   GJ_HIP(hipGetLastError());
-  version_finish(c, v, n, false);
+  version_finish(c, v, n);
 }
 
 // ---------------------------------------------------------------- renaming by degree (Sec. 5.4)

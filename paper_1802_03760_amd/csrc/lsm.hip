@@ -281,7 +281,7 @@ void graph_compact(gj_ctx* c, gj_graph* g) {
     GJ_HIP(hipGetLastError());
   }
   nv.m = m;
-  version_finish(c, nv, n, false);
+  version_finish(c, nv, n);
   g->cur = s;
   lsm_clear(c, g);
   ++c->lsm_compactions;

@@ -44,13 +44,15 @@ constexpr uint64_t kOwnerMaskMax = 4ull << 30;  // bytes of mask
 // The pairs of owner_count's sets, for listing: marks every match, counts and
 // numbers the rows of every seed edge, in workspace (`words` of mask); matches
 // and extensions as owner_count (its plan, too).  False, and nothing marked,
-// when the mask would take more than most_words.  Until the context's next
+// when extensions are below `least` or the mask would take more than
+// most_words.  Until the context's next
 // owner_mask, owner_mask_counts are the matches per seed edge, and owner_rows
 // writes the `matches` rows in seed and value order, with their columns placed
 // by map.
 bool owner_mask(gj_ctx* c, const OwnerArgs& a, const uint32_t* seed_row, const uint32_t* seed_col,
-                const uint32_t* t_row, const uint32_t* t_col, uint64_t E, uint64_t most_words, KernelTimer& timer,
-                OwnerPlan* plan, uint64_t gen, gj_ctx* pc, uint64_t& words, uint64_t& matches, uint64_t& extensions);
+                const uint32_t* t_row, const uint32_t* t_col, uint64_t E, uint64_t least,
+                uint64_t most_words, KernelTimer& timer, OwnerPlan* plan, uint64_t gen, gj_ctx* pc,
+                uint64_t& words, uint64_t& matches, uint64_t& extensions);
 void owner_rows(gj_ctx* c, const OwnerArgs& a, const uint32_t* seed_row, const uint32_t* seed_col, uint64_t E,
                 uint64_t words, const RowMap& map, uint32_t* rows);
 const uint32_t* owner_mask_counts(gj_ctx* c);

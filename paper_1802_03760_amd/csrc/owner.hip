@@ -536,13 +536,27 @@ __device__ __forceinline__ bool proposes_b(uint32_t da, uint32_t db) {
   return (da > db ? da : db) >= kDMin && db <= da;
 }
 
-__global__ void k_mask_words(OwnerArgs a, const uint32_t* __restrict__ row, const uint32_t* __restrict__ col,
-                             uint64_t E, uint32_t* __restrict__ words) {
+// words of every edge; sum: all words, all candidates, in kSumSlots parts a line
+// apart (as kDegreeSlots of graph.hip)
+constexpr uint32_t kSumSlots = 32, kSumStride = 8;
+__global__ void __launch_bounds__(kBlock) k_mask_words(OwnerArgs a, const uint32_t* __restrict__ row,
+                                                       const uint32_t* __restrict__ col, uint64_t E,
+                                                       uint32_t* __restrict__ words,
+                                                       unsigned long long* __restrict__ sum) {
   const uint64_t gs = (uint64_t)gridDim.x * blockDim.x;
+  uint64_t t[2] = {0, 0};
   for (uint64_t e = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; e < E; e += gs) {
     const uint32_t da = a.rpA[row[e] + 1] - a.rpA[row[e]], db = a.rpB[col[e] + 1] - a.rpB[col[e]];
     const uint32_t s = !da || !db ? 0 : proposes_b(da, db) ? db : da;
-    words[e] = s / 64 + (s % 64 != 0);
+    const uint32_t w = s / 64 + (s % 64 != 0);
+    words[e] = w;
+    t[0] += w;
+    t[1] += da < db ? da : db;
+  }
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const uint64_t s = block_sum<kBlock>(t[i]);
+    if (threadIdx.x == 0 && s) atomicAdd(sum + blockIdx.x % kSumSlots * kSumStride + i, (unsigned long long)s);
   }
 }
 
@@ -805,18 +819,24 @@ void owner_count(gj_ctx* c, const OwnerArgs& a, const uint32_t* seed_row, const 
 }
 
 bool owner_mask(gj_ctx* c, const OwnerArgs& a, const uint32_t* seed_row, const uint32_t* seed_col,
-                const uint32_t* t_row, const uint32_t* t_col, uint64_t E, uint64_t most_words, KernelTimer& timer,
-                OwnerPlan* plan, uint64_t gen, gj_ctx* pc, uint64_t& nw, uint64_t& matches, uint64_t& extensions) {
+                const uint32_t* t_row, const uint32_t* t_col, uint64_t E, uint64_t least, uint64_t most_words,
+                KernelTimer& timer, OwnerPlan* plan, uint64_t gen, gj_ctx* pc, uint64_t& nw, uint64_t& matches,
+                uint64_t& extensions) {
   nw = matches = extensions = 0;
   if (!E) return true;
   uint32_t* words = (uint32_t*)ws_get(c, "om_words", (E + 1) * sizeof(uint32_t));
-  uint64_t* off = (uint64_t*)ws_get(c, "om_off", (E + 1) * sizeof(uint64_t));
+  uint64_t h[kSumSlots * kSumStride], total = 0;
+  unsigned long long* sum = (unsigned long long*)ws_get(c, "om_sum", sizeof(h));
   const unsigned ge = grid_for(E, kBlock * 4, 1u << 14);
-  // 64-bit offsets first (in the row offsets' buffer): the words may exceed 32 bits
-  k_mask_words<<<ge, kBlock, 0, c->stream>>>(a, seed_row, seed_col, E, words);
-  scan_u32_to_u64(c, words, off, E);
-  nw = read_u64(c, off + E);
-  if (nw > most_words) return false;
+  GJ_HIP(hipMemsetAsync(sum, 0, sizeof(h), c->stream));
+  k_mask_words<<<std::min(ge, (unsigned)c->num_cus * 8), kBlock, 0, c->stream>>>(a, seed_row, seed_col, E, words, sum);
+  read_bytes(c, h, sum, sizeof(h));
+  for (uint32_t i = 0; i < kSumSlots; ++i) {
+    nw += h[i * kSumStride];
+    total += h[i * kSumStride + 1];
+  }
+  if (nw > most_words || total < least) return false;
+  uint64_t* off = (uint64_t*)ws_get(c, "om_off", (E + 1) * sizeof(uint64_t));
   uint32_t* woff = (uint32_t*)ws_get(c, "om_woff", (E + 1) * sizeof(uint32_t));
   scan_u32(c, words, woff, E);
   unsigned long long* mask = (unsigned long long*)ws_get(c, "om_mask", (nw + 1) * sizeof(uint64_t));
@@ -831,7 +851,6 @@ bool owner_mask(gj_ctx* c, const OwnerArgs& a, const uint32_t* seed_row, const u
   k_mask_count<<<grid_for(E, kBlock, (unsigned)c->num_cus * 32), kBlock, 0, c->stream>>>(mask, woff, E, words);
   scan_u32_to_u64(c, words, off, E);
   GJ_HIP(hipGetLastError());
-  uint64_t h[2];
   read_u64s(c, {off + E, (const uint64_t*)(l.acc + 1)}, h);
   matches = h[0];
   extensions = h[1];

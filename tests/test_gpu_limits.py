@@ -140,3 +140,43 @@ def test_edge_counts_without_room():
     through = [run(i)[0] for i in range(1, last + 1)]
     # its workspace: counts, row offsets, word offsets, mask, transposed seeds
     assert sum(through) >= 5, through
+
+
+def test_listing_workspace():
+    """A listing without candidates takes no workspace beyond its frontier's: a
+    million edges one way between two sets of vertices, and a star."""
+    import paper_1802_03760_amd as gj
+    rng = np.random.default_rng(2)
+    one_way = rng.integers(0, 1 << 16, 1 << 20), rng.integers(1 << 16, 1 << 17, 1 << 20)
+    star = np.zeros(200000, np.int64), np.arange(1, 200001)
+    for s, d in (one_way, star):
+        A = Bounded(gj)
+        ctx = gj.Context(0, allocator=A)
+        ctx.set_option("seed_chunk", 1 << 12)
+        ctx.set_option("frontier_cap", 1 << 14)
+        G = gj.Graph(ctx, s.astype(np.uint32), d.astype(np.uint32), 1 << 18)
+        E = G.info()["edges"]
+        before = A.held
+        for q in (Q.TRIANGLE, Q.CYCLIC_TRIANGLE):
+            st, rows = gj.enumerate_rows(ctx, G, gj.Query(ctx, *q), out=np.empty((8, 3), np.uint32))
+            assert st["matches"] == 0 and st["prefixes"][2] == E and st["extensions"][2] == 0
+        assert A.held - before < 4 * E, (A.held - before, E)
+
+
+def test_listing_without_room():
+    """Whole listings where device memory does not hold the mask pass's
+    workspace: the rows all the same."""
+    import paper_1802_03760_amd as gj
+    s, d = synth.rmat_draws(13, 12, seed=2)
+    want = oracle.run(oracle.Graph(1 << 13, s, d), Q.TRIANGLE, collect=True, threads=4)
+    A = Bounded(gj)
+    ctx = gj.Context(0, allocator=A)
+    for k, v in (("seed_chunk", 1 << 12), ("frontier_cap", 1 << 14), ("hash_index", 0)):
+        ctx.set_option(k, v)
+    G = gj.Graph(ctx, s, d, 1 << 13)
+    q = gj.Query(ctx, *Q.TRIANGLE)
+    out = torch.zeros((want["matches"], 3), dtype=torch.int32, device="cuda")
+    A.most = 4 * G.info()["edges"] - 1  # less than a word per edge
+    st, _ = gj.enumerate_rows(ctx, G, q, out=out)
+    same(st, want)
+    assert np.array_equal(out.cpu().numpy().view(np.uint32), want["rows"])
