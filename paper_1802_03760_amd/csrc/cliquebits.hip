@@ -45,7 +45,51 @@ constexpr uint32_t kCbCap[kCbClasses] = {64, 256, 512, 1056};
 // uniform random graphs, whose members have short rows, lose (5.2e5 edges: 367
 // -> 430 us).
 constexpr uint64_t kCbBitsEdges = 500000;
-constexpr uint32_t kCbAsIs = 16384, kCbAsIsDeg = 512;  // vertices and degree up to which ids stay as they are
+
+// Which kernels count the cliques, and in which order of the vertices.  Any
+// order counts every clique once; any of the three ways is right for any graph.
+//
+// As they are: graphs of at most kCbAsIs vertices without hubs (largest out-
+// and in-degree together at most kCbAsIsDeg), and larger ones where no vertex
+// can have more than kCbAsIsAny members.  Renaming costs 110 us, 5 us per
+// 10^5 edges and 40 per 10^6 ids, and saves nothing there: uniform graphs,
+// 4-clique, edge-grouped kernels / as they are / renamed: 16,385 vertices and
+// 65,536 edges 255 / 91 / 280 us, 2.6e5 and 2.6e5 398 / 145 / 396, 4.2e6 and
+// 1.7e7 12.9 / 4.4 / 6.3 ms.
+//
+// The edge-grouped kernels (clique.hip) where the graph is too light to repay
+// the preparation: two = sum of out^2, which bounds their first step, against
+// 36 for every edge and a sixth for every id.  R-MAT, 4-clique,
+// edge-grouped / renamed: 16,384 vertices, 16,073 edges (two = 4.2e5) 222 / 274
+// us, 65,536 and 32,000 (7.5e5) 229 / 298, 1,024 and 9,500 (1.2e6) 1017 / 257,
+// 65,536 and 65,000 (2.6e6) 510 / 402; 2.6e5 and 1.3e5 (4.7e6) 463 / 497.  In
+// id spaces of 6.7e7 with 20,000 edges 275 us / 3.4 ms, with 2e5 12.3 / 3.9 ms.
+// A 5-clique pays one workgroup's chain for its largest vertex, so light
+// graphs go there from kCbAsIsAny on (1,024 vertices, 3,600 edges: 228 us, as
+// they are 296).  Uniform graphs stay as they are up to kCbIds ids and 32 per
+// edge (4.2e6 ids, 84,000 edges 139 us / 232; 1.7e7 ids, 2,000 edges 390 /
+// 199).  Graphs built with ids ascending by degree are reversed, at a third of
+// the renaming's cost, but for small ones where nothing lies two edges deep (a
+// star of 2,000 edges 99 / 132 us, of 20,000 124 / 127, of 200,000 293 / 129).
+constexpr uint32_t kCbAsIs = 16384, kCbAsIsDeg = 512, kCbAsIsAny = 128;
+constexpr uint64_t kCbLightEdge = 36, kCbLightIds = 6, kCbIds = 1ull << 21, kCbFlat = 16384;
+
+static bool choose_order(const Version& v, uint32_t n, bool by_degree, int q, HubOrder& order) {
+  const uint64_t most = (uint64_t)v.max_deg[0] + v.max_deg[1];
+  const uint64_t two = std::min(v.two[0], v.m * std::min(v.max_deg[0], v.max_deg[1]));
+  const bool light = two < kCbLightEdge * v.m + n / kCbLightIds;
+  const bool apart = n > kCbIds + 32 * v.m;
+  if (by_degree) {
+    order = HubOrder::kReversed;
+    return (two > v.m || v.m > kCbFlat) && !(apart && light);
+  }
+  if (most <= (n <= kCbAsIs ? kCbAsIsDeg : kCbAsIsAny)) {
+    order = HubOrder::kAsIs;
+    return !(light && (apart || (q == 5 && most > kCbAsIsAny)));
+  }
+  order = HubOrder::kDegree;
+  return !light;
+}
 
 // extensions[2]: the lesser out-degree of every edge's ends
 __global__ void __launch_bounds__(kBlock) k_cb_ext2(HubGraph g, const uint32_t* __restrict__ row, uint64_t m,
@@ -531,18 +575,14 @@ bool clique_bits_count(gj_ctx* c, const Version& v, uint32_t n, bool by_degree, 
                        uint64_t out[6]) {
   for (int i = 0; i < 6; ++i) out[i] = 0;
   if (!v.m) return true;
+  HubOrder order;
+  if (!choose_order(v, n, by_degree, q, order)) return false;
   constexpr size_t kCtl = kCbAcc * 8 + (kCbClasses + 2) * 4;
   unsigned long long* acc = (unsigned long long*)ws_get(c, "cb_ctl", kCtl);
   unsigned int* len = (unsigned int*)(acc + kCbAcc);
   uint32_t* lists = (uint32_t*)ws_get(c, "cb_lists", (uint64_t)kCbClasses * n * sizeof(uint32_t));
   const unsigned cus = (unsigned)c->num_cus;
-  // Any order of the vertices counts every clique once.  Small graphs without
-  // hubs go in the order they have (16,000 vertices, 64,000 edges, uniform,
-  // 4-clique: 300 -> 149 us); with hubs the renaming is worth its sorts from
-  // about 2,000 vertices on (R-MAT-12: 445 us renamed, 724 as it is).
   const uint64_t most = (uint64_t)v.max_deg[0] + v.max_deg[1];
-  const HubOrder order = by_degree ? HubOrder::kReversed
-                         : n <= kCbAsIs && most <= kCbAsIsDeg ? HubOrder::kAsIs : HubOrder::kDegree;
   const uint32_t* row = nullptr;
   HubGraph g = hub_graph(c, v, n, order, row);
   auto classes = [&] {

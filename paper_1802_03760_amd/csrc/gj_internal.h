@@ -462,8 +462,9 @@ void edge4_count(gj_ctx* c, const Version& v, int shape, const uint32_t above[4]
 // cliquebits.hip: the transitive 4-clique or 5-clique (q = 4, 5; no
 // inequalities) over every forward edge of v: out = {matches, extensions[2],
 // prefixes[3], extensions[3], prefixes[4], extensions[4]} (the last two of the
-// 5-clique).  by_degree (here and below): ids ascend by degree.  False, and nothing counted, where some vertex has too many
-// neighbours of higher degree.
+// 5-clique).  by_degree (here and below): ids ascend by degree.  False, and
+// nothing counted, where some vertex has too many neighbours of higher degree
+// or the graph is too light to repay the preparation.
 bool clique_bits_count(gj_ctx* c, const Version& v, uint32_t n, bool by_degree, int q, KernelTimer& timer,
                        uint64_t out[6]);
 // twopath.hip: the diamond over every forward edge of v by 2-path counts (no

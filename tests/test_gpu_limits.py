@@ -180,3 +180,61 @@ def test_listing_without_room():
     st, _ = gj.enumerate_rows(ctx, G, q, out=out)
     same(st, want)
     assert np.array_equal(out.cpu().numpy().view(np.uint32), want["rows"])
+
+
+def held_by_counts(n, s, d, queries, **build):
+    """The workspace whole counts leave with their context, results checked."""
+    import paper_1802_03760_amd as gj
+    A = Bounded(gj)
+    ctx = gj.Context(0, allocator=A)
+    ctx.set_option("hash_index", 0)
+    s, d = s.astype(np.uint32), d.astype(np.uint32)
+    G = gj.Graph(ctx, s, d, n, **build)
+    if build:
+        s, d, _ = oracle.relabel_by_degree(n, s, d)
+    O = oracle.Graph(n, s, d)
+    before = A.held
+    for q in queries:
+        same(gj.count(ctx, G, gj.Query(ctx, *q)), oracle.run(O, q, threads=8), q)
+    return A.held - before, G.info()["edges"]
+
+
+@pytest.mark.parametrize("build", [{}, {"degree_order": True}])
+@pytest.mark.parametrize("graph", ["uniform", "rmat"])
+def test_cliques_ids_apart(graph, build):
+    """20,000 edges among 2^24 ids: no workspace per id."""
+    rng = np.random.default_rng(4)
+    n = 1 << 24
+    if graph == "uniform":
+        s, d = rng.integers(0, n, (2, 20000))
+    else:
+        s, d = (x.astype(np.int64) << 10 for x in synth.rmat_draws(14, 1, seed=3))
+    held, E = held_by_counts(n, s, d, [Q.CLIQUE4, Q.CLIQUE5], **build)
+    assert held < 4 * n, (held, E)
+
+
+def test_cliques_uniform_above():
+    """20,000 vertices without hubs keep their order: the prefixes and the
+    lists, and no renamed copy (32 bytes an edge and 36 a vertex more)."""
+    rng = np.random.default_rng(5)
+    n = 20000
+    held, E = held_by_counts(n, *rng.integers(0, n, (2, 80000)), [Q.CLIQUE4, Q.CLIQUE5])
+    assert held < 40 * E, (held, E)
+
+
+@pytest.mark.parametrize("build", [{}, {"degree_order": True}])
+def test_cliques_star(build):
+    """Nothing lies two edges deep: no preparation, which takes 32 bytes an edge
+    and more."""
+    k = 10000 if build else 100000
+    for s, d in ((np.zeros(k, int), 1 + np.arange(k)), (1 + np.arange(k), np.zeros(k, int))):
+        held, E = held_by_counts(k + 1, s, d, [Q.CLIQUE4, Q.CLIQUE5], **build)
+        assert held < 16 * E, (held, E)
+
+
+@pytest.mark.parametrize("draws", [1, 2, 4])
+@pytest.mark.parametrize("scale", [8, 10, 12, 14, 16])
+def test_cliques_light(scale, draws):
+    """R-MAT graphs on both sides of the lines between the ways to count."""
+    s, d = synth.rmat_draws(scale, draws, seed=scale)
+    held_by_counts(1 << scale, s, d, [Q.CLIQUE4, Q.CLIQUE5])
