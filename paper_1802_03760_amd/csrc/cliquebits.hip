@@ -74,12 +74,12 @@ constexpr uint64_t kCbBitsEdges = 500000;
 constexpr uint32_t kCbAsIs = 16384, kCbAsIsDeg = 512, kCbAsIsAny = 128;
 constexpr uint64_t kCbLightEdge = 36, kCbLightIds = 6, kCbIds = 1ull << 21, kCbFlat = 16384;
 
-static bool choose_order(const Version& v, uint32_t n, bool by_degree, int q, HubOrder& order) {
+static bool choose_order(const Version& v, uint32_t n, int q, HubOrder& order) {
   const uint64_t most = (uint64_t)v.max_deg[0] + v.max_deg[1];
   const uint64_t two = std::min(v.two[0], v.m * std::min(v.max_deg[0], v.max_deg[1]));
   const bool light = two < kCbLightEdge * v.m + n / kCbLightIds;
   const bool apart = n > kCbIds + 32 * v.m;
-  if (by_degree) {
+  if (v.ranked()) {
     order = HubOrder::kReversed;
     return (two > v.m || v.m > kCbFlat) && !(apart && light);
   }
@@ -571,12 +571,11 @@ static void launch(gj_ctx* c, const HubGraph& g, const CbBits& hb, const uint32_
   k_cb_cliques<Q, kCbCap[0], 128, 256><<<cus * 8, 256, 0, c->stream>>>(g, hb, lists, len, acc);
 }
 
-bool clique_bits_count(gj_ctx* c, const Version& v, uint32_t n, bool by_degree, int q, KernelTimer& timer,
-                       uint64_t out[6]) {
+bool clique_bits_count(gj_ctx* c, const Version& v, uint32_t n, int q, KernelTimer& timer, uint64_t out[6]) {
   for (int i = 0; i < 6; ++i) out[i] = 0;
   if (!v.m) return true;
   HubOrder order;
-  if (!choose_order(v, n, by_degree, q, order)) return false;
+  if (!choose_order(v, n, q, order)) return false;
   constexpr size_t kCtl = kCbAcc * 8 + (kCbClasses + 2) * 4;
   unsigned long long* acc = (unsigned long long*)ws_get(c, "cb_ctl", kCtl);
   unsigned int* len = (unsigned int*)(acc + kCbAcc);
@@ -595,8 +594,8 @@ bool clique_bits_count(gj_ctx* c, const Version& v, uint32_t n, bool by_degree, 
     return beyond == 0;
   };
   if (!classes()) {
-    if (order == HubOrder::kDegree) return false;
-    g = hub_graph(c, v, n, HubOrder::kDegree, row);
+    if (order != HubOrder::kReversed || !v.blur) return false;
+    g = hub_graph(c, v, n, HubOrder::kDegree, row);  // the ids no longer say who is a hub
     if (!classes()) return false;
   }
   CbBits hb{};

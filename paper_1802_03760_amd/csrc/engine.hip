@@ -627,7 +627,7 @@ void run_static(gj_ctx* c, const gj_graph* g, const gj_query* q, int mode, uint6
   if ((shape == 0 || clique5) && !P.has_ineq() && v.m < (1ull << 31) && !v.pmap[0] && !v.pmap[1]) {
     KernelTimer timer(c);
     uint64_t o[6];
-    if (clique_bits_count(c, v, g->n, g->old_of_new != nullptr, P.m, timer, o)) {
+    if (clique_bits_count(c, v, g->n, P.m, timer, o)) {
       gj_stats s{};
       s.prefixes[2] = v.m;
       s.extensions[2] = o[1];
@@ -692,9 +692,9 @@ void run_static(gj_ctx* c, const gj_graph* g, const gj_query* q, int mode, uint6
     KernelTimer timer(c);
     uint64_t o[3];
     if (cycle4)
-      cycle4_2p_count(c, v, g->n, g->old_of_new != nullptr, timer, o);
+      cycle4_2p_count(c, v, g->n, timer, o);
     else
-      diamond2p_count(c, v, g->n, g->old_of_new != nullptr, timer, o);
+      diamond2p_count(c, v, g->n, timer, o);
     gj_stats s{};
     s.prefixes[2] = v.m;
     s.extensions[2] = s.prefixes[3] = o[1];

@@ -217,6 +217,7 @@ void version_finish(gj_ctx* c, Version& v, uint32_t n) {
   k_degrees<<<grid_for(n, kBlock * 16, 1024), kBlock, 0, c->stream>>>(v.d[0].rp, v.d[1].rp, n, stats);
   GJ_HIP(hipGetLastError());
   read_bytes(c, h, stats, sizeof(h));
+  v.blur = ~0ull;
   v.max_deg[0] = v.max_deg[1] = 0;
   v.two[0] = v.two[1] = v.two[2] = 0;
   for (const DegreeStats& x : h) {
@@ -359,6 +360,7 @@ void graph_build_sym(gj_ctx* c, gj_graph* g, const uint32_t* d_src, const uint32
   }
   GJ_HIP(hipGetLastError());
   graph_build(c, g, es, ed, ms);
+  if (degree_order) g->ver[g->cur].blur = 0;
   GJ_HIP(hipStreamSynchronize(c->stream));
 }
 

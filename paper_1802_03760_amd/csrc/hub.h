@@ -28,10 +28,10 @@ struct HubGraph {
 
 constexpr uint32_t kTpHubs = 16384;  // ids below it: 8-bit counter pairs for all of them take 32 KiB
 
-// How a version's ids become hub-first: sorted by degree; reversed, for a
-// graph built with ids ascending by degree (its updates may blur that: the
-// order decides work, never results); or left as they are, for small graphs,
-// whose sorts would cost more than the order saves.
+// How a version's ids become hub-first: sorted by degree; reversed, where they
+// ascend by degree (Version::ranked(); the order decides work, never results); or
+// left as they are, for graphs whose sorts would cost more than the order
+// saves.
 enum class HubOrder { kDegree, kReversed, kAsIs };
 
 // hub.hip: version v (m > 0, fewer than 2^31 edges) under `order`, in

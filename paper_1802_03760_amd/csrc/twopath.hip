@@ -736,8 +736,7 @@ __global__ void __launch_bounds__(kTpDirectNT) k_tp_direct(HubGraph g, uint32_t*
 }
 
 // ---------------------------------------------------------------- host
-static void count_2path(gj_ctx* c, const Version& v, uint32_t n, bool by_degree, bool cycle, KernelTimer& timer,
-                        uint64_t out[3]) {
+static void count_2path(gj_ctx* c, const Version& v, uint32_t n, bool cycle, KernelTimer& timer, uint64_t out[3]) {
   for (int i = 0; i < 3; ++i) out[i] = 0;
   if (!v.m) return;
   // control words: the accumulators, the lists' lengths per pass and class,
@@ -773,7 +772,7 @@ static void count_2path(gj_ctx* c, const Version& v, uint32_t n, bool by_degree,
     return;
   }
   const uint32_t* row = nullptr;
-  HubGraph g = hub_graph(c, v, n, by_degree ? HubOrder::kReversed : HubOrder::kDegree, row);
+  HubGraph g = hub_graph(c, v, n, v.ranked() ? HubOrder::kReversed : HubOrder::kDegree, row);
   hub_above(c, g);
   uint32_t* lists = (uint32_t*)ws_get(c, "tp_lists", (uint64_t)kLists * n * sizeof(uint32_t));
   uint32_t* rec = (uint32_t*)ws_get(c, "tp_rec", 2 * (uint64_t)n * sizeof(uint32_t));
@@ -809,14 +808,12 @@ static void count_2path(gj_ctx* c, const Version& v, uint32_t n, bool by_degree,
   out[2] = h[kTpMin];
 }
 
-void diamond2p_count(gj_ctx* c, const Version& v, uint32_t n, bool by_degree, KernelTimer& timer,
-                     uint64_t out[3]) {
-  count_2path(c, v, n, by_degree, false, timer, out);
+void diamond2p_count(gj_ctx* c, const Version& v, uint32_t n, KernelTimer& timer, uint64_t out[3]) {
+  count_2path(c, v, n, false, timer, out);
 }
 
-void cycle4_2p_count(gj_ctx* c, const Version& v, uint32_t n, bool by_degree, KernelTimer& timer,
-                     uint64_t out[3]) {
-  count_2path(c, v, n, by_degree, true, timer, out);
+void cycle4_2p_count(gj_ctx* c, const Version& v, uint32_t n, KernelTimer& timer, uint64_t out[3]) {
+  count_2path(c, v, n, true, timer, out);
 }
 
 }  // namespace gj
