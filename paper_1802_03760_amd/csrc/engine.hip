@@ -627,7 +627,9 @@ void run_static(gj_ctx* c, const gj_graph* g, const gj_query* q, int mode, uint6
   if ((shape == 0 || clique5) && !P.has_ineq() && v.m < (1ull << 31) && !v.pmap[0] && !v.pmap[1]) {
     KernelTimer timer(c);
     uint64_t o[6];
-    if (clique_bits_count(c, v, g->n, P.m, timer, o)) {
+    bool counted = false;
+    ws_fits(c, {"tp_", "cb_"}, [&] { counted = clique_bits_count(c, v, g->n, P.m, timer, o); });
+    if (counted) {
       gj_stats s{};
       s.prefixes[2] = v.m;
       s.extensions[2] = o[1];
