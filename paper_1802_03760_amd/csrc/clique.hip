@@ -867,4 +867,269 @@ void clique5_count(gj_ctx* c, const Version& v, const uint32_t above[5], const u
   }
 }
 
+// ---------------------------------------------------------------- 2-path counts by dense counters
+// The diamond and the 4-cycle where twopath.hip's kernels cannot go: graphs of
+// 2^31 edges or ids and more, and where device memory does not hold their
+// renamed copy (40 bytes an edge, 120 an id, against 8 bytes an id and worker
+// here).  Bound by the atomics on the counters in HBM, 1.8e10 a second:
+// R-MAT-18 diamond 128 ms against 3.4 there.
+//
+// The diamond's matches from a0 are the pairs (a1, a2) of out(a0) with a
+// common out-neighbour a3, counted per a3: with k(a3) the number of 2-paths
+// a0 -> a1 -> a3, a0 contributes the sum of k(a3)^2 (a1 = a2 included, as
+// the join allows).  One workgroup per a0 counts its 2-path endpoints with
+// atomics in a private dense array of n counters, noting each endpoint at its
+// first visit in a private list, then takes each listed endpoint's count
+// with an exchange to zero, which leaves the array clear (one atomic per
+// distinct endpoint instead of a second walk of every 2-path).  The
+// counters are the depth-first evaluation's: extensions[2] = prefixes[3] =
+// sum of d0^2 (a2 is proposed from out(a0) alone), extensions[3] = the sum
+// over (a1, a2) in out(a0)^2 of min(d(a1), d(a2)), from tiles of the
+// neighbours' degrees in LDS.
+constexpr uint32_t kDgTile = 4096;  // degrees per LDS tile
+constexpr uint32_t kDgOff = 1024;   // a1 per offsets chunk
+
+__global__ void __launch_bounds__(kBlock) k_diamond2p(const uint32_t* __restrict__ rp,
+                                                      const uint32_t* __restrict__ col, uint32_t n,
+                                                      unsigned int* __restrict__ cnt_all, uint32_t* __restrict__ list_all,
+                                                      uint64_t cnt_stride, unsigned long long* __restrict__ claim,
+                                                      unsigned long long* __restrict__ acc) {
+  __shared__ uint32_t DA[kDgTile], DB[kDgTile];
+  __shared__ uint32_t Wp[kDgOff + 1];
+  __shared__ unsigned long long next;
+  __shared__ uint32_t s_nl;  // endpoints listed for this a0
+  unsigned int* cnt = cnt_all + (uint64_t)blockIdx.x * cnt_stride;
+  uint32_t* list = list_all + (uint64_t)blockIdx.x * cnt_stride;
+  const uint32_t tid = threadIdx.x;
+  const int lane = lane_id();
+  uint64_t matches = 0, sq = 0, ext3 = 0;
+  for (;;) {
+    __syncthreads();
+    if (tid == 0) {
+      next = atomicAdd(claim, 1ull);
+      s_nl = 0;
+    }
+    __syncthreads();
+    const unsigned long long a0 = next;
+    if (a0 >= n) break;
+    const uint32_t b0 = rp[a0], d0 = rp[a0 + 1] - b0;
+    if (d0 == 0) continue;
+    if (tid == 0) sq += (uint64_t)d0 * d0;
+    // extensions[3]: sum over ordered pairs of min(degree), in tiles
+    for (uint32_t ta = 0; ta < d0; ta += kDgTile) {
+      const uint32_t na = d0 - ta < kDgTile ? d0 - ta : kDgTile;
+      __syncthreads();
+      for (uint32_t i = tid; i < na; i += kBlock) {
+        uint32_t v = col[b0 + ta + i];
+        DA[i] = rp[v + 1] - rp[v];
+      }
+      for (uint32_t tb = 0; tb < d0; tb += kDgTile) {
+        const uint32_t nb = d0 - tb < kDgTile ? d0 - tb : kDgTile;
+        __syncthreads();
+        for (uint32_t i = tid; i < nb; i += kBlock) {
+          uint32_t v = col[b0 + tb + i];
+          DB[i] = rp[v + 1] - rp[v];
+        }
+        __syncthreads();
+        for (uint32_t i = tid; i < na; i += kBlock) {
+          const uint32_t x = DA[i];
+          uint64_t s = 0;
+          for (uint32_t j = 0; j < nb; ++j) {
+            uint32_t y = DB[j];
+            s += y < x ? y : x;
+          }
+          ext3 += s;
+        }
+      }
+    }
+    // the 2-paths: count their endpoints, listing each at its first visit
+    for (uint32_t c0 = 0; c0 < d0; c0 += kDgOff) {
+      const uint32_t cn = d0 - c0 < kDgOff ? d0 - c0 : kDgOff;
+      uint32_t run = 0;
+      for (uint32_t t = 0; t < cn; t += kBlock) {
+        uint32_t i = t + tid, w = 0;
+        if (i < cn) {
+          uint32_t a1 = col[b0 + c0 + i];
+          w = rp[a1 + 1] - rp[a1];
+        }
+        uint32_t tot = 0;
+        uint32_t ex = block_excl_scan<kBlock>(w, tot);
+        if (i < cn) Wp[i] = run + ex;
+        run += tot;
+      }
+      if (tid == 0) Wp[cn] = run;
+      __syncthreads();
+      for (uint32_t q0 = 0; q0 < run; q0 += kBlock) {  // the whole wave takes every step
+        const uint32_t q = q0 + tid;
+        uint32_t a3 = 0;
+        bool first = false;
+        if (q < run) {
+          uint32_t i = lds_owner(Wp, cn, q);  // i < cn: Wp[cn] = run > q
+          uint32_t a1 = col[b0 + c0 + i];
+          a3 = col[rp[a1] + (q - Wp[i])];
+          first = atomicAdd(cnt + a3, 1u) == 0u;
+        }
+        const uint64_t fm = __ballot(first);
+        if (fm) {
+          uint32_t base = 0;
+          if (lane == 0) base = atomicAdd(&s_nl, (uint32_t)__popcll(fm));
+          base = __shfl(base, 0, 64);
+          if (first) list[base + (uint32_t)__popcll(fm & lanemask_lt())] = a3;
+        }
+      }
+      __syncthreads();
+    }
+    // every count and list entry of this a0 is in before any is taken back
+    __threadfence();
+    __syncthreads();
+    const uint32_t nl = s_nl;
+    for (uint32_t i = tid; i < nl; i += kBlock) {
+      const uint64_t k = atomicExch(cnt + list[i], 0u);
+      matches += k * k;
+    }
+  }
+  uint64_t v[3] = {matches, sq, ext3};
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    uint64_t t = block_sum<kBlock>(v[i]);
+    if (tid == 0 && t) atomicAdd(acc + i, (unsigned long long)t);
+  }
+}
+
+void diamond2p_dense(gj_ctx* c, const Version& v, uint32_t n, KernelTimer& timer, uint64_t out[3]) {
+  const CsrDir& d = v.d[0];
+  // one dense counter array and one endpoint list per workgroup, at most
+  // 16 GiB in all
+  uint64_t per = ((uint64_t)n + 63) / 64 * 64;
+  uint64_t wgs = std::min<uint64_t>((uint64_t)c->num_cus * 2, std::max<uint64_t>(1, (16ull << 30) / (per * 8)));
+  unsigned int* cnt = (unsigned int*)ws_get(c, "dg_cnt", wgs * per * sizeof(unsigned int));
+  uint32_t* list = (uint32_t*)ws_get(c, "dg_list", wgs * per * sizeof(uint32_t));
+  unsigned long long* ctr = (unsigned long long*)ws_get(c, "dg_ctr", 4 * sizeof(unsigned long long));
+  GJ_HIP(hipMemsetAsync(cnt, 0, wgs * per * sizeof(unsigned int), c->stream));
+  GJ_HIP(hipMemsetAsync(ctr, 0, 4 * sizeof(unsigned long long), c->stream));
+  timer.start();
+  k_diamond2p<<<(unsigned)wgs, kBlock, 0, c->stream>>>(d.rp, d.col, n, cnt, list, per, ctr, ctr + 1);
+  timer.stop();
+  GJ_HIP(hipGetLastError());
+  unsigned long long h[4];
+  read_bytes(c, h, ctr, sizeof(h));
+  for (int i = 0; i < 3; ++i) out[i] = h[1 + i];
+}
+
+// The 4-cycle edge(a0,a1), edge(a1,a2), edge(a2,a3), edge(a3,a0): the
+// matches from a0 pair each forward 2-path a0 -> a1 -> a2 with each backward
+// one a2 -> a3 -> a0 of the same a2, so a0 contributes the sum over a2 of
+// k(a2) k'(a2) (forward times backward 2-path counts).  One workgroup per a0
+// adds the forward 2-paths' endpoints into its private counters (listing
+// each endpoint at its first visit), walks the backward 2-paths (through
+// the reverse index) summing the counters they reach, and clears the listed
+// endpoints.  Counters as the
+// depth-first evaluation: extensions[2] = prefixes[3] = the forward 2-paths
+// (a2 is proposed from out(a1) alone), extensions[3] = the sum over them of
+// min(|out(a2)|, |in(a0)|).
+
+// Calls f(a1, a2) for every 2-path a0 -> a1 -> a2 with a1 in col1[b0, b0 + d0)
+// and a2 in the row of a1 in (rp2, col2), over the workgroup.
+template <class F>
+__device__ __forceinline__ void walk_2paths(const uint32_t* __restrict__ col1, uint32_t b0, uint32_t d0,
+                                            const uint32_t* __restrict__ rp2, const uint32_t* __restrict__ col2,
+                                            uint32_t* Wp, F f) {
+  const uint32_t tid = threadIdx.x;
+  for (uint32_t c0 = 0; c0 < d0; c0 += kDgOff) {
+    const uint32_t cn = d0 - c0 < kDgOff ? d0 - c0 : kDgOff;
+    uint32_t run = 0;
+    for (uint32_t t = 0; t < cn; t += kBlock) {
+      uint32_t i = t + tid, w = 0;
+      if (i < cn) {
+        uint32_t a1 = col1[b0 + c0 + i];
+        w = rp2[a1 + 1] - rp2[a1];
+      }
+      uint32_t tot = 0;
+      uint32_t ex = block_excl_scan<kBlock>(w, tot);
+      if (i < cn) Wp[i] = run + ex;
+      run += tot;
+    }
+    if (tid == 0) Wp[cn] = run;
+    __syncthreads();
+    for (uint32_t q = tid; q < run; q += kBlock) {
+      uint32_t i = lds_owner(Wp, cn, q);  // i < cn: Wp[cn] = run > q
+      uint32_t a1 = col1[b0 + c0 + i];
+      f(a1, col2[rp2[a1] + (q - Wp[i])]);
+    }
+    __syncthreads();
+  }
+}
+
+__global__ void __launch_bounds__(kBlock) k_cycle4_2p(const uint32_t* __restrict__ rpf,
+                                                      const uint32_t* __restrict__ colf,
+                                                      const uint32_t* __restrict__ rpr,
+                                                      const uint32_t* __restrict__ colr, uint32_t n,
+                                                      unsigned int* __restrict__ cnt_all, uint32_t* __restrict__ list_all,
+                                                      uint64_t cnt_stride, unsigned long long* __restrict__ claim,
+                                                      unsigned long long* __restrict__ acc) {
+  __shared__ uint32_t Wp[kDgOff + 1];
+  __shared__ unsigned long long next;
+  __shared__ uint32_t s_nl;  // forward endpoints listed for this a0
+  unsigned int* cnt = cnt_all + (uint64_t)blockIdx.x * cnt_stride;
+  uint32_t* list = list_all + (uint64_t)blockIdx.x * cnt_stride;
+  const uint32_t tid = threadIdx.x;
+  uint64_t matches = 0, paths = 0, ext3 = 0;
+  for (;;) {
+    __syncthreads();
+    if (tid == 0) {
+      next = atomicAdd(claim, 1ull);
+      s_nl = 0;
+    }
+    __syncthreads();
+    const unsigned long long a0 = next;
+    if (a0 >= n) break;
+    const uint32_t bo = rpf[a0], dout = rpf[a0 + 1] - bo, bi = rpr[a0], din = rpr[a0 + 1] - bi;
+    if (dout == 0) continue;
+    walk_2paths(colf, bo, dout, rpf, colf, Wp, [&](uint32_t, uint32_t a2) {
+      if (atomicAdd(cnt + a2, 1u) == 0u) list[atomicAdd(&s_nl, 1u)] = a2;  // first visit: listed
+      uint32_t d2 = rpf[a2 + 1] - rpf[a2];
+      ext3 += d2 < din ? d2 : din;
+      paths += 1;
+    });
+    __threadfence();
+    __syncthreads();
+    if (din)
+      walk_2paths(colr, bi, din, rpr, colr, Wp, [&](uint32_t, uint32_t a2) {
+        matches += __hip_atomic_load(cnt + a2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // at L2
+      });
+    __syncthreads();
+    // clear the listed endpoints (one store each instead of a third walk)
+    const uint32_t nl = s_nl;
+    for (uint32_t i = tid; i < nl; i += kBlock)
+      __hip_atomic_store(cnt + list[i], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __threadfence();
+    __syncthreads();
+  }
+  uint64_t v[3] = {matches, paths, ext3};
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    uint64_t t = block_sum<kBlock>(v[i]);
+    if (tid == 0 && t) atomicAdd(acc + i, (unsigned long long)t);
+  }
+}
+
+void cycle4_2p_dense(gj_ctx* c, const Version& v, uint32_t n, KernelTimer& timer, uint64_t out[3]) {
+  uint64_t per = ((uint64_t)n + 63) / 64 * 64;
+  // one counter array and one endpoint list per workgroup, at most 16 GiB in all
+  uint64_t wgs = std::min<uint64_t>((uint64_t)c->num_cus * 2, std::max<uint64_t>(1, (16ull << 30) / (per * 8)));
+  unsigned int* cnt = (unsigned int*)ws_get(c, "dg_cnt", wgs * per * sizeof(unsigned int));
+  uint32_t* list = (uint32_t*)ws_get(c, "dg_list", wgs * per * sizeof(uint32_t));
+  unsigned long long* ctr = (unsigned long long*)ws_get(c, "dg_ctr", 4 * sizeof(unsigned long long));
+  GJ_HIP(hipMemsetAsync(cnt, 0, wgs * per * sizeof(unsigned int), c->stream));
+  GJ_HIP(hipMemsetAsync(ctr, 0, 4 * sizeof(unsigned long long), c->stream));
+  timer.start();
+  k_cycle4_2p<<<(unsigned)wgs, kBlock, 0, c->stream>>>(v.d[0].rp, v.d[0].col, v.d[1].rp, v.d[1].col, n, cnt, list,
+                                                        per, ctr, ctr + 1);
+  timer.stop();
+  GJ_HIP(hipGetLastError());
+  unsigned long long h[4];
+  read_bytes(c, h, ctr, sizeof(h));
+  for (int i = 0; i < 3; ++i) out[i] = h[1 + i];
+}
+
 }  // namespace gj

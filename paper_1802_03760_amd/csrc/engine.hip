@@ -688,15 +688,19 @@ void run_static(gj_ctx* c, const gj_graph* g, const gj_query* q, int mode, uint6
                 P.bind[3].size() == 2 &&
                 ((is_bind(P.bind[3][0], 2, 0) && is_bind(P.bind[3][1], 0, 1)) ||
                  (is_bind(P.bind[3][1], 2, 0) && is_bind(P.bind[3][0], 0, 1)));
-  // diamond / 4-cycle: 2-path counts per pair (their index arithmetic takes
-  // fewer than 2^31 edges)
-  if (((shape == 1 && !P.has_ineq()) || cycle4) && v.m < (1ull << 31)) {
+  // diamond / 4-cycle: 2-path counts, per pair of renamed vertices (their index
+  // arithmetic takes fewer than 2^31 edges and ids) or else per dense counter
+  if ((shape == 1 && !P.has_ineq()) || cycle4) {
     KernelTimer timer(c);
     uint64_t o[3];
-    if (cycle4)
-      cycle4_2p_count(c, v, g->n, timer, o);
-    else
-      diamond2p_count(c, v, g->n, timer, o);
+    const bool counted = v.m < (1ull << 31) && g->n < (1u << 31) && ws_fits(c, {"tp_"}, [&] {
+      if (cycle4)
+        cycle4_2p_count(c, v, g->n, timer, o);
+      else
+        diamond2p_count(c, v, g->n, timer, o);
+    });
+    if (!counted && cycle4) cycle4_2p_dense(c, v, g->n, timer, o);
+    if (!counted && !cycle4) diamond2p_dense(c, v, g->n, timer, o);
     gj_stats s{};
     s.prefixes[2] = v.m;
     s.extensions[2] = s.prefixes[3] = o[1];

@@ -488,6 +488,9 @@ void clique5_count(gj_ctx* c, const Version& v, const uint32_t above[5], const u
 // 2-path counts (no inequalities): out = {matches, prefixes[3] =
 // extensions[2], extensions[3]}.
 void cycle4_2p_count(gj_ctx* c, const Version& v, uint32_t n, KernelTimer& timer, uint64_t out[3]);
+// clique.hip: both with a dense counter per vertex and worker, for any graph
+void diamond2p_dense(gj_ctx* c, const Version& v, uint32_t n, KernelTimer& timer, uint64_t out[3]);
+void cycle4_2p_dense(gj_ctx* c, const Version& v, uint32_t n, KernelTimer& timer, uint64_t out[3]);
 // tri.hip: the triangle relation of the graph's current version (replaces
 // g->tri); frees it
 void tri_index_build(gj_ctx* c, gj_graph* g);

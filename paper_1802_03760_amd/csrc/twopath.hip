@@ -774,14 +774,14 @@ static void count_2path(gj_ctx* c, const Version& v, uint32_t n, bool cycle, Ker
   const uint32_t* row = nullptr;
   HubGraph g = hub_graph(c, v, n, v.ranked() ? HubOrder::kReversed : HubOrder::kDegree, row);
   hub_above(c, g);
-  uint32_t* lists = (uint32_t*)ws_get(c, "tp_lists", (uint64_t)kLists * n * sizeof(uint32_t));
+  const int passes = cycle ? 1 : 2;
+  uint32_t* lists = (uint32_t*)ws_get(c, "tp_lists", (uint64_t)passes * kTpClasses * n * sizeof(uint32_t));
   uint32_t* rec = (uint32_t*)ws_get(c, "tp_rec", 2 * (uint64_t)n * sizeof(uint32_t));
   GJ_HIP(hipMemsetAsync(rec, 0, 2 * (uint64_t)n * sizeof(uint32_t), c->stream));
   timer.start();
   const unsigned gn = grid_for(n, kBlock, cus * 8);
   k_hub_recip<<<grid_for(v.m, kBlock, cus * 32), kBlock, 0, c->stream>>>(g, row, v.m, rec, rec + n);
   k_hub_terms<<<gn, kBlock, 0, c->stream>>>(g, rec, rec + n, cycle ? 1 : 0, acc);
-  const int passes = cycle ? 1 : 2;
   k_hub_classes<<<grid_for(n, 64, cus * 16), kBlock, 0, c->stream>>>(g, cycle ? 1 : 0, len, lists, n, acc);
   for (int p = 0; p < passes; ++p) {
     const int op = cycle || p ? 1 : 0;

@@ -259,3 +259,25 @@ def test_cliques_without_room():
     for q in (Q.CLIQUE4, Q.CLIQUE5):
         same(gj.count(ctx, G, gj.Query(ctx, *q)), oracle.run(O, q, threads=8), q)
     assert A.held > before + 8 * E  # the refused workspace was not kept
+
+
+@pytest.mark.parametrize("kind,query", [("diamond", Q.DIAMOND), ("cycle4", Q.CYCLE4)])
+def test_twopath_without_room(kind, query):
+    """Whole diamonds and 4-cycles where device memory does not hold the renamed
+    graph: dense counters (8 bytes an id and worker) count."""
+    import paper_1802_03760_amd as gj
+    n, m = 4096, 2000000
+    rng = np.random.default_rng(6)
+    s, d = rng.integers(0, n, (2, m)).astype(np.uint32)
+    s[:4000], d[:4000] = 7, 50 + np.arange(4000)  # degrees beyond the small graphs' kernel
+    s[4000:8000], d[4000:8000] = 60 + np.arange(4000), 7
+    want = oracle.twopath(oracle.Graph(n, s, d), kind, threads=8)
+    A = Bounded(gj)
+    ctx = gj.Context(0, allocator=A)
+    G = gj.Graph(ctx, s, d, n)
+    q = gj.Query(ctx, *query)
+    A.most = 7 * G.info()["edges"]  # no 64-bit key per edge; 512 workers' counters fit
+    same(gj.count(ctx, G, q), want)
+    assert A.refused
+    A.most = None
+    same(gj.count(ctx, G, q), want)
