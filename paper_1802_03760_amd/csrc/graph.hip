@@ -104,27 +104,75 @@ __global__ void k_split_keys(const uint64_t* __restrict__ keys, uint64_t m, uint
   }
 }
 
-// rp[v] = first entry of row v in a row-sorted entry list (rp[n] = m), by a
-// search per vertex: bound by its chain of some 26 loads, 163 us a direction
-// at 4.2e6 vertices and 6.7e7 entries, and the same whatever the rows.  (An
-// entry that writes the starts of the rows it ends takes 142 us there, but
-// leaves a long run of empty rows to one wave: 4.2e6 vertices without edges
-// 2 ms a direction against 15 us.)
-__global__ void k_rowptr(const uint32_t* __restrict__ row, uint64_t m, uint32_t n, uint32_t* __restrict__ rp) {
-  uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-  for (uint64_t v = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; v <= n; v += stride) {
-    uint64_t lo = 0, len = m;
-    while (len > 0) {
-      uint64_t half = len >> 1;
-      if (row[lo + half] < v) {
-        lo += half + 1;
-        len -= half + 1;
-      } else {
-        len = half;
-      }
-    }
-    rp[v] = (uint32_t)lo;
+// first e in [0, m) with row[e] >= x (row ascending), else m; by the whole wave
+__device__ __forceinline__ uint64_t wave_lower(const uint32_t* __restrict__ row, uint64_t m, uint64_t x) {
+  uint64_t lo = 0, len = m;
+  while (len > 0) {
+    const uint64_t step = (len + 63) / 64, at = lane_id() * step;
+    const uint64_t below = __ballot(at < len && row[lo + at] < x);  // lanes 0..k-1
+    const uint64_t k = (uint64_t)__popcll(below);
+    if (!k) break;
+    const uint64_t next = k * step < len ? k * step : len;  // not below, or the end
+    lo += (k - 1) * step + 1;
+    len = next - ((k - 1) * step + 1);
   }
+  return lo;
+}
+
+// rp[v] = first entry of row v in a row-sorted entry list (rp[n] = m): entry
+// e starts the rows after its predecessor's up to its own (and entry m those
+// up to n).  Runs of empty rows longer than a few are filled by the whole
+// wave, but for the chunks of kRowChunk rows that lie inside one run: those
+// have a wave each, the workgroups from `entries` on, so that a wave fills at
+// most two chunks of a run.  Builds of 4.2e6 vertices without edges: 92 us
+// with a search per vertex, 4.05 ms where one wave fills a run, 97 us so; of
+// as many with 1,000 edges 264, 562 and 242 (399 at chunks of 4,096 rows),
+// with 6.4e7 edges 5.06, 5.02 and 5.02 ms.
+constexpr uint64_t kRowChunk = 512;
+
+__global__ void __launch_bounds__(kBlock) k_rowptr(const uint32_t* __restrict__ row, uint64_t m, uint32_t n,
+                                                   unsigned entries, uint32_t* __restrict__ rp) {
+  constexpr uint64_t kAlone = 8;
+  const uint64_t rows = (uint64_t)n + 1;
+  if (blockIdx.x >= entries) {
+    const uint64_t waves = (uint64_t)(gridDim.x - entries) * (kBlock / 64);
+    for (uint64_t a = ((uint64_t)(blockIdx.x - entries) * (kBlock / 64) + wave_id()) * kRowChunk; a < rows;
+         a += waves * kRowChunk) {
+      const uint64_t b = a + kRowChunk < rows ? a + kRowChunk : rows;
+      const uint64_t e = wave_lower(row, m, a);
+      if (e == m || (uint64_t)row[e] + 1 >= b)
+        for (uint64_t v = a + lane_id(); v < b; v += 64) rp[v] = (uint32_t)e;
+    }
+    return;
+  }
+  const uint64_t stride = (uint64_t)entries * kBlock;
+  for (uint64_t b = (uint64_t)blockIdx.x * kBlock; b <= m; b += stride) {  // whole waves take every step
+    const uint64_t e = b + threadIdx.x;
+    uint64_t lo = 0, hi = 0;  // rows [lo, hi) start at e
+    if (e <= m) {
+      lo = e ? (uint64_t)row[e - 1] + 1 : 0;
+      hi = e < m ? (uint64_t)row[e] + 1 : rows;
+    }
+    const bool big = hi > lo + kAlone;
+    if (!big)
+      for (; lo < hi; ++lo) rp[lo] = (uint32_t)e;
+    for (uint64_t left = __ballot(big); left; left &= left - 1) {
+      const int src = __ffsll((unsigned long long)left) - 1;
+      const uint64_t l = shfl_u64(lo, src), h = shfl_u64(hi, src), x = shfl_u64(e, src);
+      // the whole chunks in [l, h): from c0 to c1 (the last chunk ends at rows)
+      uint64_t c0 = (l + kRowChunk - 1) / kRowChunk * kRowChunk;
+      uint64_t c1 = h == rows ? rows : h / kRowChunk * kRowChunk;
+      if (c0 > c1 || c0 >= rows) c0 = c1 = h;
+      for (uint64_t v = l + lane_id(); v < c0; v += 64) rp[v] = (uint32_t)x;
+      for (uint64_t v = c1 + lane_id(); v < h; v += 64) rp[v] = (uint32_t)x;
+    }
+  }
+}
+
+static void row_pointers(gj_ctx* c, const uint32_t* row, uint64_t m, uint32_t n, uint32_t* rp) {
+  const unsigned entries = grid_for(m + 1, kBlock, 1u << 16);
+  const unsigned chunks = grid_for((uint64_t)n + 1, kRowChunk * (kBlock / 64), 1u << 16);
+  k_rowptr<<<entries + chunks, kBlock, 0, c->stream>>>(row, m, n, entries, rp);
 }
 
 // Largest degrees of both directions, and the sums over the vertices of out^2,
@@ -212,8 +260,7 @@ void version_finish(gj_ctx* c, Version& v, uint32_t n) {
   DegreeStats h[kDegreeSlots];
   DegreeStats* stats = (DegreeStats*)ws_get(c, "degrees", sizeof(h));
   GJ_HIP(hipMemsetAsync(stats, 0, sizeof(h), c->stream));
-  for (int d = 0; d < 2; ++d)
-    k_rowptr<<<grid_for((uint64_t)n + 1, kBlock, 1u << 16), kBlock, 0, c->stream>>>(v.d[d].row, v.m, n, v.d[d].rp);
+  for (int d = 0; d < 2; ++d) row_pointers(c, v.d[d].row, v.m, n, v.d[d].rp);
   k_degrees<<<grid_for(n, kBlock * 16, 1024), kBlock, 0, c->stream>>>(v.d[0].rp, v.d[1].rp, n, stats);
   GJ_HIP(hipGetLastError());
   read_bytes(c, h, stats, sizeof(h));
@@ -345,7 +392,7 @@ void graph_build_sym(gj_ctx* c, gj_graph* g, const uint32_t* d_src, const uint32
     uint64_t* vk2 = (uint64_t*)alloc((uint64_t)n * sizeof(uint64_t));
     uint32_t* new_of_old = (uint32_t*)alloc((uint64_t)n * sizeof(uint32_t));
     unsigned gn = grid_for((uint64_t)n + 1, kBlock, 1u << 16);
-    k_rowptr<<<gn, kBlock, 0, c->stream>>>(srow, ms, n, rp);
+    row_pointers(c, srow, ms, n, rp);
     k_degree_keys<<<gn, kBlock, 0, c->stream>>>(rp, n, vk);
     uint64_t* vs = sort_u64(c, vk, vk2, n, 0, bits);  // stable: equal degrees by id
     g->old_of_new = (uint32_t*)dev_alloc(c, (uint64_t)n * sizeof(uint32_t));
