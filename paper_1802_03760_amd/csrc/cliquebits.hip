@@ -37,7 +37,7 @@ namespace gj {
 // matches, then pre and ext per stage: kCb + 2 (j - 2) and + 1 for |P_j|, j >= 3
 enum { kCbMatches, kCbExt2, kCbPre3, kCbExt3, kCbPre4, kCbExt4, kCbAcc };
 constexpr int kCbClasses = 4;
-constexpr uint32_t kCbCap[kCbClasses] = {64, 256, 512, 1056};
+constexpr uint32_t kCbCap[kCbClasses] = {64, 256, 512, kBigDegree};
 // Edges from which the hubs' adjacency bits are built, where some vertex has
 // more than kCbCap[0] neighbours below it.  Their build is some 40 us: R-MAT-15
 // (3.2e5 edges) 4-clique 795 -> 729 us and 5-clique 1,481 -> 1,487, R-MAT-16
@@ -108,8 +108,10 @@ __global__ void __launch_bounds__(kBlock) k_cb_ext2(HubGraph g, const uint32_t* 
 // counts those beyond the last class.  A neighbour both ways counts twice, but
 // for the last class: R-MAT-22 has 380 vertices of more than 1,056 neighbours
 // so counted, none of more than 1,049 (its 4-clique: 16.4 s on the
-// edge-grouped kernels, 0.12 s here).
-__global__ void __launch_bounds__(kBlock) k_cb_classes(HubGraph g, unsigned int* __restrict__ len,
+// edge-grouped kernels, 0.12 s here).  fits: none is beyond, as is known; else
+// the two rows of such a vertex are merged, by one thread (0.4 ms for rows of
+// 1,040 entries each).
+__global__ void __launch_bounds__(kBlock) k_cb_classes(HubGraph g, int fits, unsigned int* __restrict__ len,
                                                        uint32_t* __restrict__ lists) {
   __shared__ uint32_t cnt[kCbClasses + 1], base[kCbClasses + 1];
   for (uint64_t b = (uint64_t)blockIdx.x * kBlock; b < g.n; b += (uint64_t)gridDim.x * kBlock) {
@@ -123,7 +125,9 @@ __global__ void __launch_bounds__(kBlock) k_cb_classes(HubGraph g, unsigned int*
       if (d >= 2) {
         c = 0;
         while (c < kCbClasses && d > kCbCap[c]) ++c;
-        if (c == kCbClasses && d <= 2 * kCbCap[c - 1]) {
+        if (fits && c == kCbClasses) {
+          --c;
+        } else if (c == kCbClasses && d <= 2 * kCbCap[c - 1]) {
           uint64_t i = g.rp[0][v], j = g.rp[1][v], both = 0;  // rows ascend
           while (i < g.end[0][v] && j < g.end[1][v]) {
             const uint32_t x = g.col[0][i], y = g.col[1][j];
@@ -583,21 +587,20 @@ bool clique_bits_count(gj_ctx* c, const Version& v, uint32_t n, int q, KernelTim
   const unsigned cus = (unsigned)c->num_cus;
   const uint64_t most = (uint64_t)v.max_deg[0] + v.max_deg[1];
   const uint32_t* row = nullptr;
-  HubGraph g = hub_graph(c, v, n, order, row);
-  auto classes = [&] {
+  HubGraph g;
+  auto prepare = [&](HubOrder o) {
+    if (!hub_graph(c, v, n, o, true, g, row)) return false;
     GJ_HIP(hipMemsetAsync(acc, 0, kCtl, c->stream));
-    k_cb_classes<<<grid_for(n, kBlock, cus * 8), kBlock, 0, c->stream>>>(g, len, lists);
+    const bool fits = o != HubOrder::kReversed || (!v.blur && !hub_limit_open(v));
+    k_cb_classes<<<grid_for(n, kBlock, cus * 8), kBlock, 0, c->stream>>>(g, fits ? 1 : 0, len, lists);
     GJ_HIP(hipGetLastError());
-    if (most <= kCbCap[kCbClasses - 1]) return true;
+    if (fits) return true;
     unsigned int beyond = 0;
     read_bytes(c, &beyond, len + kCbClasses, sizeof(beyond));
     return beyond == 0;
   };
-  if (!classes()) {
-    if (order != HubOrder::kReversed || !v.blur) return false;
-    g = hub_graph(c, v, n, HubOrder::kDegree, row);  // the ids no longer say who is a hub
-    if (!classes()) return false;
-  }
+  // reversed ids that changes have blurred may say too little of who is a hub
+  if (!prepare(order) && (order != HubOrder::kReversed || !v.blur || !prepare(HubOrder::kDegree))) return false;
   CbBits hb{};
   if (v.m >= kCbBitsEdges && most > kCbCap[0]) {
     // quads of the two directions end to end: does any vertex have an in-prefix?

@@ -504,7 +504,7 @@ void apply_updates(gj_ctx* c, gj_graph* g, const uint32_t* src, const uint32_t* 
     ++nv.gen;  // written (as version_finish marks a slot)
     nv.max_deg[0] = h3[1];
     nv.max_deg[1] = h3[2];
-    nv.two[0] = nv.two[1] = nv.two[2] = ~0ull;
+    nv.two[0] = nv.two[1] = nv.two[2] = nv.big = ~0ull;
     nv.blur = bv.blur == ~0ull || L.on ? ~0ull : bv.blur + k;
   }
   const Version& ov = patched ? lsm_old : cur_view;

@@ -130,6 +130,8 @@ struct OwnerPlan {
   const uint32_t* key[4] = {nullptr, nullptr, nullptr, nullptr};
 };
 
+constexpr uint32_t kBigDegree = 1056;  // members of a bit matrix at most (cliquebits.hip)
+
 struct Version {
   CsrDir d[2];  // 0 forward, 1 reverse
   uint64_t m = 0, cap = 0;
@@ -138,6 +140,7 @@ struct Version {
   // a build or a compaction; ~0 after an update.  They bound the work of a
   // count or listing before it starts; results never depend on them.
   uint64_t two[3] = {~0ull, ~0ull, ~0ull};
+  uint64_t big = ~0ull;  // likewise: vertices of more than kBigDegree edges
   // edge changes since the ids were given out in ascending order of degree;
   // ~0 where they never were
   uint64_t blur = ~0ull;

@@ -175,14 +175,14 @@ static void row_pointers(gj_ctx* c, const uint32_t* row, uint64_t m, uint32_t n,
   k_rowptr<<<entries + chunks, kBlock, 0, c->stream>>>(row, m, n, entries, rp);
 }
 
-// Largest degrees of both directions, and the sums over the vertices of out^2,
-// in^2 and out x in: a few atomics per workgroup, into one of kDegreeSlots
+// Largest degrees of both directions, the sums over the vertices of out^2,
+// in^2 and out x in, and how many have more than kBigDegree edges: a few atomics per workgroup, into one of kDegreeSlots
 // lines (a thousand workgroups' on one address are some 25 us), which the
 // host adds up.
 constexpr int kDegreeSlots = 32;
 struct alignas(64) DegreeStats {
   uint32_t most[2];
-  unsigned long long two[3];
+  unsigned long long two[4];  // the last: the vertices of many edges
 };
 
 __global__ void __launch_bounds__(kBlock) k_degrees(const uint32_t* __restrict__ rp0,
@@ -191,7 +191,7 @@ __global__ void __launch_bounds__(kBlock) k_degrees(const uint32_t* __restrict__
   __shared__ uint32_t wbest[2][kBlock / 64];
   out += blockIdx.x % kDegreeSlots;
   uint32_t best[2] = {0, 0};
-  uint64_t two[3] = {0, 0, 0};
+  uint64_t two[4] = {0, 0, 0, 0};
   uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
   for (uint64_t v = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n; v += stride) {
     const uint32_t d0 = rp0[v + 1] - rp0[v], d1 = rp1[v + 1] - rp1[v];
@@ -200,9 +200,10 @@ __global__ void __launch_bounds__(kBlock) k_degrees(const uint32_t* __restrict__
     two[0] += (uint64_t)d0 * d0;
     two[1] += (uint64_t)d1 * d1;
     two[2] += (uint64_t)d0 * d1;
+    two[3] += (uint64_t)d0 + d1 > kBigDegree ? 1 : 0;
   }
 #pragma unroll
-  for (int i = 0; i < 3; ++i) {
+  for (int i = 0; i < 4; ++i) {
     const uint64_t t = block_sum<kBlock>(two[i]);
     if (threadIdx.x == 0 && t) atomicAdd(&out->two[i], (unsigned long long)t);
   }
@@ -266,10 +267,11 @@ void version_finish(gj_ctx* c, Version& v, uint32_t n) {
   read_bytes(c, h, stats, sizeof(h));
   v.blur = ~0ull;
   v.max_deg[0] = v.max_deg[1] = 0;
-  v.two[0] = v.two[1] = v.two[2] = 0;
+  v.two[0] = v.two[1] = v.two[2] = v.big = 0;
   for (const DegreeStats& x : h) {
     for (int d = 0; d < 2; ++d) v.max_deg[d] = std::max(v.max_deg[d], x.most[d]);
     for (int i = 0; i < 3; ++i) v.two[i] += x.two[i];
+    v.big += x.two[3];
   }
 }
 

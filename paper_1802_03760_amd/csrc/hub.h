@@ -34,9 +34,20 @@ constexpr uint32_t kTpHubs = 16384;  // ids below it: 8-bit counter pairs for al
 // saves.
 enum class HubOrder { kDegree, kReversed, kAsIs };
 
+// May some vertex have more than kBigDegree different neighbours below it, by
+// degree?  It and they have more than kBigDegree edges each, so a graph with
+// one has more such vertices than that, and 559,153 edges or more.
+inline bool hub_limit_open(const Version& v) {
+  return v.big > kBigDegree && (uint64_t)v.max_deg[0] + v.max_deg[1] > kBigDegree &&
+         v.m >= (kBigDegree + 1ull) * (kBigDegree + 2) / 2;
+}
+
 // hub.hip: version v (m > 0, fewer than 2^31 edges) under `order`, in
-// workspace of the context; row receives the row of every out-entry
-HubGraph hub_graph(gj_ctx* c, const Version& v, uint32_t n, HubOrder order, const uint32_t*& row);
+// workspace of the context; row receives the row of every out-entry.  limit,
+// looked at when sorting by degree only: false, before the edges are sorted,
+// where some vertex has more than kBigDegree different neighbours below it.
+bool hub_graph(gj_ctx* c, const Version& v, uint32_t n, HubOrder order, bool limit, HubGraph& g,
+               const uint32_t*& row);
 void hub_above(gj_ctx* c, HubGraph& g);  // fills g.mq
 
 __device__ __forceinline__ uint32_t lane_value(uint32_t v, int lane) {

@@ -16,24 +16,87 @@ __global__ void k_hub_keys(const uint32_t* __restrict__ rp0, const uint32_t* __r
   }
 }
 
-// new id = position in descending degree order; degrees in the new order
+// new id = position in descending degree order; degrees in the new order;
+// lim[0]: the vertices of more than cap edges
 __global__ void k_hub_ids(const uint64_t* __restrict__ keys, const uint32_t* __restrict__ rp0,
                           const uint32_t* __restrict__ rp1, uint32_t n, uint32_t* __restrict__ new_of_old,
-                          uint32_t* __restrict__ d0, uint32_t* __restrict__ d1) {
+                          uint32_t* __restrict__ d0, uint32_t* __restrict__ d1, uint64_t cap,
+                          unsigned int* __restrict__ lim) {
   const uint64_t gs = (uint64_t)gridDim.x * blockDim.x;
   for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gs) {
     const uint32_t o = (uint32_t)keys[i];
     new_of_old[o] = (uint32_t)i;
-    d0[i] = rp0[o + 1] - rp0[o];
-    d1[i] = rp1[o + 1] - rp1[o];
+    const uint32_t a = rp0[o + 1] - rp0[o], b = rp1[o + 1] - rp1[o];
+    d0[i] = a;
+    d1[i] = b;
+    if (lim && (uint64_t)a + b > cap) {  // the last of these says how many they are
+      const uint32_t next = i + 1 < n ? (uint32_t)keys[i + 1] : 0;
+      if (i + 1 == n || (uint64_t)(rp0[next + 1] - rp0[next]) + (rp1[next + 1] - rp1[next]) <= cap)
+        lim[0] = (unsigned int)i + 1;
+    }
   }
 }
 
-__global__ void k_hub_edges(const uint32_t* __restrict__ row, const uint32_t* __restrict__ col, uint64_t m,
-                            const uint32_t* __restrict__ new_of_old, uint64_t* __restrict__ keys) {
+// LIMIT: below[v], for v in (cap, lim[0]), counts the edges between v and
+// vertices below it (the others have no more than cap of either); a row's own
+// by one atomic per wave, rows being sorted.
+template <bool LIMIT>
+__global__ void __launch_bounds__(kBlock) k_hub_edges(const uint32_t* __restrict__ row,
+                                                      const uint32_t* __restrict__ col, uint64_t m,
+                                                      const uint32_t* __restrict__ new_of_old,
+                                                      uint64_t* __restrict__ keys,
+                                                      uint32_t cap, const unsigned int* __restrict__ lim,
+                                                      uint32_t* __restrict__ below) {
   const uint64_t gs = (uint64_t)gridDim.x * blockDim.x;
-  for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < m; i += gs)
-    keys[i] = ((uint64_t)new_of_old[row[i]] << 32) | new_of_old[col[i]];
+  const uint32_t big = LIMIT ? lim[0] : 0;
+  for (uint64_t b = (uint64_t)blockIdx.x * blockDim.x; b < m; b += gs) {  // whole waves take every step
+    const uint64_t i = b + threadIdx.x;
+    uint32_t u = ~0u, v = ~0u;
+    if (i < m) {
+      u = new_of_old[row[i]];
+      v = new_of_old[col[i]];
+      keys[i] = ((uint64_t)u << 32) | v;
+    }
+    if (LIMIT) {
+      if (v < big && v > cap && u < v) atomicAdd(below + v, 1u);
+      const bool mine = u < big && u > cap && v < u;
+      for (uint64_t left = __ballot(mine); left;) {
+        const int first = __ffsll((unsigned long long)left) - 1;
+        const uint32_t fu = __shfl(u, first, 64);
+        const uint64_t same = __ballot(mine && u == fu);
+        if (lane_id() == first) atomicAdd(below + fu, (uint32_t)__popcll(same));
+        left &= ~same;
+      }
+    }
+  }
+}
+
+// lim[1]: the vertices with more than cap different neighbours below them.
+// One that is a neighbour both ways was counted twice, so a workgroup looks
+// those of v's row up in the other, where that can make the difference.
+__global__ void __launch_bounds__(kBlock) k_hub_limit(const uint64_t* __restrict__ keys,
+                                                      const uint32_t* __restrict__ rp0,
+                                                      const uint32_t* __restrict__ col0,
+                                                      const uint32_t* __restrict__ rp1,
+                                                      const uint32_t* __restrict__ col1,
+                                                      const uint32_t* __restrict__ new_of_old,
+                                                      const uint32_t* __restrict__ below, uint32_t cap,
+                                                      unsigned int* __restrict__ lim) {
+  const uint32_t big = lim[0];
+  for (uint32_t v = cap + 1 + blockIdx.x; v < big; v += gridDim.x) {
+    const uint32_t b = below[v];
+    if (b <= cap) continue;
+    uint64_t both = 0;
+    if (b <= 2 * cap) {
+      const uint32_t o = (uint32_t)keys[v], lo = rp1[o], hi = rp1[o + 1];
+      for (uint64_t i = (uint64_t)rp0[o] + threadIdx.x; i < rp0[o + 1]; i += kBlock) {
+        const uint32_t x = col0[i];
+        if (new_of_old[x] < v && contains_u32(col1, lo, hi, x)) ++both;
+      }
+      both = block_sum<kBlock>(both);
+    }
+    if (threadIdx.x == 0 && b - both > cap) atomicAdd(lim + 1, 1u);
+  }
 }
 
 // rows and columns of the sorted keys, and the swapped keys for the other
@@ -126,9 +189,10 @@ void hub_above(gj_ctx* c, HubGraph& g) {
   g.mq[1] = mq + g.n;
 }
 
-HubGraph hub_graph(gj_ctx* c, const Version& v, uint32_t n, HubOrder order, const uint32_t*& row) {
+bool hub_graph(gj_ctx* c, const Version& v, uint32_t n, HubOrder order, bool limit, HubGraph& g,
+               const uint32_t*& row) {
   const uint64_t m = v.m;
-  HubGraph g{};
+  g = HubGraph{};
   g.n = n;
   const unsigned gn = grid_for(n, kBlock, 1u << 14), ge = grid_for(m, kBlock * 4, 1u << 14);
   auto words = [&](const std::string& name, uint64_t count) {
@@ -143,13 +207,16 @@ HubGraph hub_graph(gj_ctx* c, const Version& v, uint32_t n, HubOrder order, cons
     }
   } else {
     uint32_t *rp[2], *orow[2], *ocol[2];
-    for (int s = 0; s < 2; ++s) {
-      const std::string z = s ? "1" : "0";
-      g.rp[s] = rp[s] = words("rp" + z, (uint64_t)n + 1);
-      g.col[s] = ocol[s] = words("col" + z, m + 1);
-      rows[s] = orow[s] = words("row" + z, m + 1);
-    }
+    auto copies = [&] {
+      for (int s = 0; s < 2; ++s) {
+        const std::string z = s ? "1" : "0";
+        g.rp[s] = rp[s] = words("rp" + z, (uint64_t)n + 1);
+        g.col[s] = ocol[s] = words("col" + z, m + 1);
+        rows[s] = orow[s] = words("row" + z, m + 1);
+      }
+    };
     if (order == HubOrder::kReversed) {
+      copies();
       for (int s = 0; s < 2; ++s)
         k_hub_reverse<<<ge, kBlock, 0, c->stream>>>(v.d[s].rp, v.d[s].row, v.d[s].col, m, n, rp[s], orow[s], ocol[s]);
     } else {
@@ -162,8 +229,27 @@ HubGraph hub_graph(gj_ctx* c, const Version& v, uint32_t n, HubOrder order, cons
       const uint32_t top = v.max_deg[0] + v.max_deg[1];
       k_hub_keys<<<gn, kBlock, 0, c->stream>>>(v.d[0].rp, v.d[1].rp, n, top, vk);
       const uint64_t* vs = sort_u64(c, vk, vk2, n, 0, bits_for(top + 1));  // stable: equal degrees by id
-      k_hub_ids<<<gn, kBlock, 0, c->stream>>>(vs, v.d[0].rp, v.d[1].rp, n, ids, deg, deg + n);
-      k_hub_edges<<<ge, kBlock, 0, c->stream>>>(v.d[0].row, v.d[0].col, m, ids, keys);
+      constexpr uint32_t cap = kBigDegree;
+      limit = limit && hub_limit_open(v);
+      unsigned int* lim = nullptr;
+      if (limit) {
+        const uint64_t most = std::min<uint64_t>(n, 2 * m / cap);  // vertices of more than cap edges
+        lim = words("lim", 2 + most);
+        GJ_HIP(hipMemsetAsync(lim, 0, (2 + most) * sizeof(uint32_t), c->stream));
+      }
+      k_hub_ids<<<gn, kBlock, 0, c->stream>>>(vs, v.d[0].rp, v.d[1].rp, n, ids, deg, deg + n, cap, lim);
+      if (limit) {
+        k_hub_edges<true><<<ge, kBlock, 0, c->stream>>>(v.d[0].row, v.d[0].col, m, ids, keys, cap, lim, lim + 2);
+        k_hub_limit<<<c->num_cus * 8, kBlock, 0, c->stream>>>(vs, v.d[0].rp, v.d[0].col, v.d[1].rp, v.d[1].col, ids,
+                                                              lim + 2, cap, lim);
+        GJ_HIP(hipGetLastError());
+        unsigned int beyond = 0;
+        read_bytes(c, &beyond, lim + 1, sizeof(beyond));
+        if (beyond) return false;
+      } else {
+        k_hub_edges<false><<<ge, kBlock, 0, c->stream>>>(v.d[0].row, v.d[0].col, m, ids, keys, 0, nullptr, nullptr);
+      }
+      copies();
       const int bits = bits_for(n);
       for (int s = 0; s < 2; ++s) {
         scan_u32(c, deg + (uint64_t)s * n, rp[s], n);
@@ -193,7 +279,7 @@ HubGraph hub_graph(gj_ctx* c, const Version& v, uint32_t n, HubOrder order, cons
   k_hub_quads<<<ge, kBlock, 0, c->stream>>>(g, rows[0], rows[1], m, (uint32_t*)pre);
   GJ_HIP(hipGetLastError());
   row = rows[0];
-  return g;
+  return true;
 }
 
 }  // namespace gj

@@ -772,7 +772,8 @@ static void count_2path(gj_ctx* c, const Version& v, uint32_t n, bool cycle, Ker
     return;
   }
   const uint32_t* row = nullptr;
-  HubGraph g = hub_graph(c, v, n, v.ranked() ? HubOrder::kReversed : HubOrder::kDegree, row);
+  HubGraph g;
+  hub_graph(c, v, n, v.ranked() ? HubOrder::kReversed : HubOrder::kDegree, false, g, row);
   hub_above(c, g);
   const int passes = cycle ? 1 : 2;
   uint32_t* lists = (uint32_t*)ws_get(c, "tp_lists", (uint64_t)passes * kTpClasses * n * sizeof(uint32_t));

@@ -187,7 +187,8 @@ def held_by_counts(n, s, d, queries, **build):
     import paper_1802_03760_amd as gj
     A = Bounded(gj)
     ctx = gj.Context(0, allocator=A)
-    ctx.set_option("hash_index", 0)
+    for k, v in (("hash_index", 0), ("frontier_cap", 1 << 14), ("seed_chunk", 1 << 12)):
+        ctx.set_option(k, v)
     s, d = s.astype(np.uint32), d.astype(np.uint32)
     G = gj.Graph(ctx, s, d, n, **build)
     if build:
@@ -281,3 +282,22 @@ def test_twopath_without_room(kind, query):
     assert A.refused
     A.most = None
     same(gj.count(ctx, G, q), want)
+
+
+@pytest.mark.parametrize("both", [False, True])
+def test_cliques_beyond(both):
+    """1,100 vertices each joined to 1,100 of as many edges: left to the
+    edge-grouped kernels before the edges are sorted (a renamed copy and its
+    prefixes take 60 bytes an edge, the keys to be sorted 16).  Both ways, with
+    550 neighbours each, they are few enough to stay."""
+    import paper_1802_03760_amd as gj
+    k = 550 if both else 1100
+    s = np.repeat(np.arange(k), k)
+    d = k + np.tile(np.arange(k), k)
+    if both:
+        s, d = np.concatenate([s, d]), np.concatenate([d, s])
+    extra = np.random.default_rng(7).integers(0, 2 * k, (2, 3000))  # some cliques
+    s, d = np.concatenate([s, extra[0]]), np.concatenate([d, extra[1]])
+    held, E = held_by_counts(2 * k, s, d, [Q.CLIQUE4] if both else [Q.CLIQUE4, Q.CLIQUE5])
+    if not both:
+        assert held < 32 * E, (held, E)
