@@ -691,23 +691,41 @@ void run_static(gj_ctx* c, const gj_graph* g, const gj_query* q, int mode, uint6
   // diamond / 4-cycle: 2-path counts, per pair of renamed vertices (their index
   // arithmetic takes fewer than 2^31 edges and ids) or else per dense counter
   if ((shape == 1 && !P.has_ineq()) || cycle4) {
-    KernelTimer timer(c);
     uint64_t o[3];
-    const bool counted = v.m < (1ull << 31) && g->n < (1u << 31) && ws_fits(c, {"tp_"}, [&] {
+    double ms = 0;
+    uint64_t launches = 0;
+    auto renamed = [&](bool force) {
+      KernelTimer timer(c);
+      const bool done = cycle4 ? cycle4_2p_count(c, v, g->n, force, timer, o)
+                               : diamond2p_count(c, v, g->n, force, timer, o);
+      if (done) {
+        ms = timer.total_ms();
+        launches = timer.launches();
+      }
+      return done;
+    };
+    auto dense = [&] {
+      KernelTimer timer(c);
       if (cycle4)
-        cycle4_2p_count(c, v, g->n, timer, o);
+        cycle4_2p_dense(c, v, g->n, timer, o);
       else
-        diamond2p_count(c, v, g->n, timer, o);
-    });
-    if (!counted && cycle4) cycle4_2p_dense(c, v, g->n, timer, o);
-    if (!counted && !cycle4) diamond2p_dense(c, v, g->n, timer, o);
+        diamond2p_dense(c, v, g->n, timer, o);
+      ms = timer.total_ms();
+      launches = timer.launches();
+    };
+    bool done = false;
+    const bool fits = v.m < (1ull << 31) && g->n < (1u << 31) && ws_fits(c, {"tp_"}, [&] { done = renamed(false); });
+    if (!fits)
+      dense();
+    else if (!done && !ws_fits(c, {"dg_"}, dense))
+      renamed(true);
     gj_stats s{};
     s.prefixes[2] = v.m;
     s.extensions[2] = s.prefixes[3] = o[1];
     s.extensions[3] = o[2];
     s.matches = s.prefixes[4] = o[0];
-    s.kernel_ms = timer.total_ms();
-    s.kernel_launches = timer.launches();
+    s.kernel_ms = ms;
+    s.kernel_launches = launches;
     *st = s;
     return;
   }

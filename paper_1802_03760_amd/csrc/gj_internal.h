@@ -317,6 +317,25 @@ class KernelTimer {
   size_t n_ = 0;
 };
 
+// An event of one call.
+class HostEvent {
+ public:
+  HostEvent() = default;
+  HostEvent(const HostEvent&) = delete;
+  HostEvent& operator=(const HostEvent&) = delete;
+  ~HostEvent() {
+    if (ev_) (void)hipEventDestroy(ev_);
+  }
+  void record(hipStream_t s) {
+    if (!ev_) GJ_HIP(hipEventCreateWithFlags(&ev_, hipEventDisableTiming));
+    GJ_HIP(hipEventRecord(ev_, s));
+  }
+  void wait() { GJ_HIP(hipEventSynchronize(ev_)); }
+
+ private:
+  hipEvent_t ev_ = nullptr;
+};
+
 // workspace buffers up to this size are retired rather than freed when they grow
 constexpr size_t kWsRetireMax = 256ull << 20;
 void* ws_get(gj_ctx* c, const std::string& name, size_t bytes);
@@ -479,7 +498,9 @@ void edge4_count(gj_ctx* c, const Version& v, int shape, const uint32_t above[4]
 bool clique_bits_count(gj_ctx* c, const Version& v, uint32_t n, int q, KernelTimer& timer, uint64_t out[6]);
 // twopath.hip: the diamond over every forward edge of v by 2-path counts (no
 // inequalities): out = {matches, prefixes[3] = extensions[2], extensions[3]}.
-void diamond2p_count(gj_ctx* c, const Version& v, uint32_t n, KernelTimer& timer, uint64_t out[3]);
+// False, and nothing counted, where the dense counters below are sooner (never
+// with `force`).
+bool diamond2p_count(gj_ctx* c, const Version& v, uint32_t n, bool force, KernelTimer& timer, uint64_t out[3]);
 // the transitive 5-clique by seed edge (forward CSR): out = matches,
 // prefixes[2], extensions[2], prefixes[3], extensions[3], prefixes[4],
 // extensions[4] of the seeds it took; the others (x0, x1: n_left pairs, in
@@ -490,7 +511,7 @@ void clique5_count(gj_ctx* c, const Version& v, const uint32_t above[5], const u
 // twopath.hip: the 4-cycle a0 -> a1 -> a2 -> a3 -> a0 by forward and backward
 // 2-path counts (no inequalities): out = {matches, prefixes[3] =
 // extensions[2], extensions[3]}.
-void cycle4_2p_count(gj_ctx* c, const Version& v, uint32_t n, KernelTimer& timer, uint64_t out[3]);
+bool cycle4_2p_count(gj_ctx* c, const Version& v, uint32_t n, bool force, KernelTimer& timer, uint64_t out[3]);
 // clique.hip: both with a dense counter per vertex and worker, for any graph
 void diamond2p_dense(gj_ctx* c, const Version& v, uint32_t n, KernelTimer& timer, uint64_t out[3]);
 void cycle4_2p_dense(gj_ctx* c, const Version& v, uint32_t n, KernelTimer& timer, uint64_t out[3]);

@@ -41,7 +41,7 @@
 namespace gj {
 
 // Accumulators of one call.
-enum { kTpAB, kTpOI, kTpRec2, kTpBoth, kTpMid, kTpRecUp2, kTpPaths, kTpMin, kTpAcc };
+enum { kTpAB, kTpOI, kTpRec2, kTpBoth, kTpMid, kTpRecUp2, kTpPaths, kTpMin, kTpWalk, kTpSegs, kTpAcc };
 
 // ---------------------------------------------------------------- reciprocal pairs
 // Per vertex, its reciprocal neighbours (rec) and those below it (rec_lo):
@@ -80,7 +80,7 @@ __global__ void __launch_bounds__(kBlock) k_hub_recip(HubGraph g, const uint32_t
 __global__ void __launch_bounds__(kBlock) k_hub_terms(HubGraph g, const uint32_t* __restrict__ rec,
                                                       const uint32_t* __restrict__ rec_lo, int cycle,
                                                       unsigned long long* __restrict__ acc) {
-  uint64_t rec2 = 0, both = 0, mid = 0, up2 = 0, paths = 0;
+  uint64_t rec2 = 0, both = 0, mid = 0, up2 = 0, paths = 0, walk = 0;
   const uint64_t gs = (uint64_t)gridDim.x * blockDim.x;
   for (uint64_t v = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; v < g.n; v += gs) {
     const uint64_t r = rec[v], lo = rec_lo[v];
@@ -91,11 +91,12 @@ __global__ void __launch_bounds__(kBlock) k_hub_terms(HubGraph g, const uint32_t
     mid += in_up * out_up - (r - lo);
     up2 += (r - lo) * (r - lo);
     paths += cycle ? in * out : out * out;
+    walk += in * out;
   }
-  const uint64_t t[5] = {rec2, both, mid, up2, paths};
-  const int at[5] = {kTpRec2, kTpBoth, kTpMid, kTpRecUp2, kTpPaths};
+  const uint64_t t[6] = {rec2, both, mid, up2, paths, walk};
+  const int at[6] = {kTpRec2, kTpBoth, kTpMid, kTpRecUp2, kTpPaths, kTpWalk};
 #pragma unroll
-  for (int i = 0; i < 5; ++i) {
+  for (int i = 0; i < 6; ++i) {
     const uint64_t s = block_sum<kBlock>(t[i]);
     if (threadIdx.x == 0 && s) atomicAdd(acc + at[i], (unsigned long long)s);
   }
@@ -116,8 +117,12 @@ __global__ void __launch_bounds__(kBlock) k_hub_terms(HubGraph g, const uint32_t
 // without being measured.  A w without neighbours on one side has no A B and
 // no O I; one with a single neighbour has A + B = 1 at every entry of its
 // walk and is summed here.
+// A w of the last two takes a step for every kTpSeg3 or kTpSeg4 ids below it,
+// whatever its entries: count_2path adds the steps up (kTpSegs) against the
+// 2-paths (kTpWalk).
 constexpr int kTpClasses = 5;
 constexpr uint32_t kTpWave = 512, kTpAbove = 1024, kTpProbe = 512;
+constexpr int kTpSeg3 = 32768, kTpSeg4 = 16384;
 
 // A workgroup classes 64 vertices, 16 lanes to each for its walk's length,
 // and takes its places in the lists with one atomic per pass and class.
@@ -129,7 +134,7 @@ __global__ void __launch_bounds__(kBlock) k_hub_classes(HubGraph g, int cycle, u
   __shared__ int8_t cls_s[2][64];
   const uint32_t sub = threadIdx.x & 15, grp = threadIdx.x / 16;
   const int passes = cycle ? 1 : 2;
-  uint64_t ones = 0;
+  uint64_t ones = 0, segs = 0;
   for (uint64_t b = (uint64_t)blockIdx.x * 64; b < g.n; b += (uint64_t)gridDim.x * 64) {
     for (uint32_t k = 0; k < 4; ++k) {
       const uint32_t slot = k * 16 + grp;
@@ -176,6 +181,7 @@ __global__ void __launch_bounds__(kBlock) k_hub_classes(HubGraph g, int cycle, u
             else if (deg[0] <= 255 && deg[1] <= 255 && above <= kTpAbove) cls = above ? 2 : 1;
             else if (deg[0] <= 65535 && deg[1] <= 65535) cls = 3;
             else cls = 4;
+            if (cls >= 3) segs += (w + (cls == 3 ? kTpSeg3 : kTpSeg4) - 1) / (cls == 3 ? kTpSeg3 : kTpSeg4);
           }
           cls_s[p][slot] = (int8_t)cls;
         }
@@ -201,6 +207,8 @@ __global__ void __launch_bounds__(kBlock) k_hub_classes(HubGraph g, int cycle, u
   }
   ones = block_sum<kBlock>(ones);
   if (threadIdx.x == 0 && ones) atomicAdd(acc + kTpAB, (unsigned long long)ones);
+  segs = block_sum<kBlock>(segs);
+  if (threadIdx.x == 0 && segs) atomicAdd(acc + kTpSegs, (unsigned long long)segs);
 }
 
 // ---------------------------------------------------------------- the walk
@@ -736,9 +744,24 @@ __global__ void __launch_bounds__(kTpDirectNT) k_tp_direct(HubGraph g, uint32_t*
 }
 
 // ---------------------------------------------------------------- host
-static void count_2path(gj_ctx* c, const Version& v, uint32_t n, bool cycle, KernelTimer& timer, uint64_t out[3]) {
+// Large graphs without hubs have many w of hundreds of thousands of ids below
+// them and a few thousand entries each: a step of k_hub_dense is 4.2 us of one
+// of 256 CUs however few of them it counts.  The dense counters of clique.hip
+// take a 2-path in 0.11 ns and an id in 70, or for the 4-cycle, which walks
+// them twice, 200; so they count where the steps, in 2-paths, are more.
+// Uniform graphs, diamond, here / dense counters: 1.0e6 vertices of 48 edges
+// 541 / 311 ms, 2.1e6 of 64 2,206 / 959, 4.2e6 of 32 2,401 / 781; 1.0e6 of 96
+// 781 / 1,002; 4-cycle: 2.1e6 of 64 1,072 / 1,688, 4.2e6 of 32 1,095 / 1,869.
+// Up to kTpFewIds there are two steps to a w at most, and nobody asks.
+constexpr uint64_t kTpStep = 145, kTpId = 640, kTpIdCycle = 1800;
+constexpr uint32_t kTpFewIds = 65536;
+
+// force: whatever the dense counters would take; else false, and nothing
+// counted, where they are the sooner
+static bool count_2path(gj_ctx* c, const Version& v, uint32_t n, bool cycle, bool force, KernelTimer& timer,
+                        uint64_t out[3]) {
   for (int i = 0; i < 3; ++i) out[i] = 0;
-  if (!v.m) return;
+  if (!v.m) return true;
   // control words: the accumulators, the lists' lengths per pass and class,
   // then the long rows of the stage-3 counter and their claim counter
   constexpr int kLists = 2 * kTpClasses;
@@ -769,7 +792,7 @@ static void count_2path(gj_ctx* c, const Version& v, uint32_t n, bool cycle, Ker
     out[0] = h[kTpAB];
     out[1] = h[kTpPaths];
     out[2] = h[kTpMin];
-    return;
+    return true;
   }
   const uint32_t* row = nullptr;
   HubGraph g;
@@ -784,16 +807,12 @@ static void count_2path(gj_ctx* c, const Version& v, uint32_t n, bool cycle, Ker
   k_hub_recip<<<grid_for(v.m, kBlock, cus * 32), kBlock, 0, c->stream>>>(g, row, v.m, rec, rec + n);
   k_hub_terms<<<gn, kBlock, 0, c->stream>>>(g, rec, rec + n, cycle ? 1 : 0, acc);
   k_hub_classes<<<grid_for(n, 64, cus * 16), kBlock, 0, c->stream>>>(g, cycle ? 1 : 0, len, lists, n, acc);
-  for (int p = 0; p < passes; ++p) {
-    const int op = cycle || p ? 1 : 0;
-    unsigned long long* a = acc + (p ? kTpOI : kTpAB);
-    const uint32_t* l = lists + (uint64_t)p * kTpClasses * n;
-    const unsigned int* ln = len + p * kTpClasses;
-    k_hub_dense<32, 16384><<<cus, 1024, 0, c->stream>>>(g, p, op, l + 4ull * n, ln + 4, a);
-    k_hub_dense<16, 32768><<<cus, 1024, 0, c->stream>>>(g, p, op, l + 3ull * n, ln + 3, a);
-    k_hub_small<true><<<cus * 4, kBlock, 0, c->stream>>>(g, p, op, l + 2ull * n, ln + 2, a);
-    k_hub_small<false><<<cus * 4, kBlock, 0, c->stream>>>(g, p, op, l + 1ull * n, ln + 1, a);
-    k_hub_wave<<<cus * 4, kBlock, 0, c->stream>>>(g, p, op, l, ln, a);
+  const bool ask = n > kTpFewIds && !force;
+  HostEvent asked;
+  unsigned long long* now = (unsigned long long*)c->pinned;
+  if (ask) {  // the stage-3 counter's kernels run while the host waits
+    GJ_HIP(hipMemcpyAsync(now, acc + kTpWalk, 2 * sizeof(*now), hipMemcpyDeviceToHost, c->stream));
+    asked.record(c->stream);
   }
   if (std::max(v.max_deg[0], v.max_deg[1]) < (1u << 22))
     k_hub_min_rows<uint32_t><<<cus * 8, kBlock, 0, c->stream>>>(g, first, big, nbig, acc + kTpMin);
@@ -801,20 +820,39 @@ static void count_2path(gj_ctx* c, const Version& v, uint32_t n, bool cycle, Ker
     k_hub_min_rows<uint64_t><<<cus * 8, kBlock, 0, c->stream>>>(g, first, big, nbig, acc + kTpMin);
   if (long_rows)
     k_hub_min_big<<<cus * 4, kBlock, 0, c->stream>>>(g, first, big, nbig, nbig + 1, overs, over, acc + kTpMin);
+  if (ask) {
+    asked.wait();
+    if ((cycle ? 2 * now[0] + kTpIdCycle * n : now[0] + kTpId * n) < kTpStep * now[1]) {
+      timer.stop();
+      return false;
+    }
+  }
+  for (int p = 0; p < passes; ++p) {
+    const int op = cycle || p ? 1 : 0;
+    unsigned long long* a = acc + (p ? kTpOI : kTpAB);
+    const uint32_t* l = lists + (uint64_t)p * kTpClasses * n;
+    const unsigned int* ln = len + p * kTpClasses;
+    k_hub_dense<32, kTpSeg4><<<cus, 1024, 0, c->stream>>>(g, p, op, l + 4ull * n, ln + 4, a);
+    k_hub_dense<16, kTpSeg3><<<cus, 1024, 0, c->stream>>>(g, p, op, l + 3ull * n, ln + 3, a);
+    k_hub_small<true><<<cus * 4, kBlock, 0, c->stream>>>(g, p, op, l + 2ull * n, ln + 2, a);
+    k_hub_small<false><<<cus * 4, kBlock, 0, c->stream>>>(g, p, op, l + 1ull * n, ln + 1, a);
+    k_hub_wave<<<cus * 4, kBlock, 0, c->stream>>>(g, p, op, l, ln, a);
+  }
   timer.stop();
   GJ_HIP(hipGetLastError());
   read_bytes(c, h, acc, sizeof(h));
   out[0] = cycle ? 4 * h[kTpAB] + 2 * h[kTpRecUp2] : h[kTpAB] + 2 * (h[kTpOI] - h[kTpBoth]) + h[kTpRec2] + h[kTpMid];
   out[1] = h[kTpPaths];
   out[2] = h[kTpMin];
+  return true;
 }
 
-void diamond2p_count(gj_ctx* c, const Version& v, uint32_t n, KernelTimer& timer, uint64_t out[3]) {
-  count_2path(c, v, n, false, timer, out);
+bool diamond2p_count(gj_ctx* c, const Version& v, uint32_t n, bool force, KernelTimer& timer, uint64_t out[3]) {
+  return count_2path(c, v, n, false, force, timer, out);
 }
 
-void cycle4_2p_count(gj_ctx* c, const Version& v, uint32_t n, KernelTimer& timer, uint64_t out[3]) {
-  count_2path(c, v, n, true, timer, out);
+bool cycle4_2p_count(gj_ctx* c, const Version& v, uint32_t n, bool force, KernelTimer& timer, uint64_t out[3]) {
+  return count_2path(c, v, n, true, force, timer, out);
 }
 
 }  // namespace gj
