@@ -59,11 +59,15 @@ constexpr uint64_t kCbBitsEdges = 500000;
 //
 // The edge-grouped kernels (clique.hip) where the graph is too light to repay
 // the preparation: two = sum of out^2, which bounds their first step, against
-// 36 for every edge and a sixth for every id.  R-MAT, 4-clique,
-// edge-grouped / renamed: 16,384 vertices, 16,073 edges (two = 4.2e5) 222 / 274
-// us, 65,536 and 32,000 (7.5e5) 229 / 298, 1,024 and 9,500 (1.2e6) 1017 / 257,
-// 65,536 and 65,000 (2.6e6) 510 / 402; 2.6e5 and 1.3e5 (4.7e6) 463 / 497.  In
-// id spaces of 6.7e7 with 20,000 edges 275 us / 3.4 ms, with 2e5 12.3 / 3.9 ms.
+// 36 for every edge (64 with more than 24 ids to each) and a sixth for every
+// id.  R-MAT, 4-clique, edge-grouped / renamed: 16,384 vertices, 16,073 edges
+// (two = 4.2e5) 222 / 274 us, 65,536 and 32,000 (7.5e5) 229 / 298, 1,024 and
+// 9,500 (1.2e6) 1017 / 257, 65,536 and 65,000 (2.6e6) 510 / 402; 2.6e5 and
+// 1.3e5 (4.7e6) 463 / 497.  From
+// 2^19 edges and one per eight ids on no graph is light: an edge costs them 0.8
+// ns at least, and 0.4 to rename (1.0e6 vertices and 3.4e7 edges, uniform: 25.8
+// / 14 ms).  In id spaces of 6.7e7 with 20,000 edges 275 us / 3.4 ms, with 2e5
+// (two = 117 an edge) 12.3 / 3.9 ms; of 3.4e7 with 1.0e6 (48) 1.1 / 2.5 ms.
 // A 5-clique pays one workgroup's chain for its largest vertex, so light
 // graphs go there from kCbAsIsAny on (1,024 vertices, 3,600 edges: 228 us, as
 // they are 296).  Uniform graphs stay as they are up to kCbIds ids and 32 per
@@ -72,12 +76,14 @@ constexpr uint64_t kCbBitsEdges = 500000;
 // the renaming's cost, but for small ones where nothing lies two edges deep (a
 // star of 2,000 edges 99 / 132 us, of 20,000 124 / 127, of 200,000 293 / 129).
 constexpr uint32_t kCbAsIs = 16384, kCbAsIsDeg = 512, kCbAsIsAny = 128;
-constexpr uint64_t kCbLightEdge = 36, kCbLightIds = 6, kCbIds = 1ull << 21, kCbFlat = 16384;
+constexpr uint64_t kCbLightEdge = 36, kCbLightApart = 64, kCbLightIds = 6, kCbLightMost = 1ull << 19;
+constexpr uint64_t kCbIds = 1ull << 21, kCbFlat = 16384;
 
 static bool choose_order(const Version& v, uint32_t n, int q, HubOrder& order) {
   const uint64_t most = (uint64_t)v.max_deg[0] + v.max_deg[1];
   const uint64_t two = std::min(v.two[0], v.m * std::min(v.max_deg[0], v.max_deg[1]));
-  const bool light = two < kCbLightEdge * v.m + n / kCbLightIds;
+  const uint64_t each = n > 24 * v.m ? kCbLightApart : kCbLightEdge;
+  const bool light = two < each * v.m + n / kCbLightIds && v.m < kCbLightMost + n / 8;
   const bool apart = n > kCbIds + 32 * v.m;
   if (v.ranked()) {
     order = HubOrder::kReversed;

@@ -301,3 +301,14 @@ def test_cliques_beyond(both):
     held, E = held_by_counts(2 * k, s, d, [Q.CLIQUE4] if both else [Q.CLIQUE4, Q.CLIQUE5])
     if not both:
         assert held < 32 * E, (held, E)
+
+
+def test_cliques_not_light():
+    """6e5 edges of 30 to a vertex are past any light graph: renamed (32 bytes an
+    edge and more of workspace), and as right as the edge-grouped kernels."""
+    rng = np.random.default_rng(8)
+    n = 20000
+    s, d = rng.integers(0, n, (2, 30 * n))
+    s[:200], d[:200] = 5, 100 + np.arange(200)  # a hub, so that the order matters
+    held, E = held_by_counts(n, s, d, [Q.CLIQUE4, Q.CLIQUE5])
+    assert E > 1 << 19 and held > 32 * E, (held, E)
