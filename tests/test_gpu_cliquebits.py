@@ -67,3 +67,24 @@ def test_hub_bits(oriented):
     d = np.concatenate([at[base + rng.integers(0, 80, len(base))], at[rng.integers(0, 120, 8000)]])
     assert len(np.unique(s.astype(np.uint64) << np.uint64(32) | d)) > 600000
     check(n, s, d, **({"degree_order": True} if oriented else {}))
+
+
+@pytest.mark.parametrize("k", [66, 130, 150])
+@pytest.mark.parametrize("way", ["down", "up", "mixed"])
+def test_dense_rows(way, k):
+    """k vertices, nine in ten pairs joined one way: matrix rows of up to 64, of
+    up to 128 and of more members, in the ids' order and against it (all members
+    out-, or all in-neighbours) and in any; and ten pairs both ways."""
+    rng = np.random.default_rng(k)
+    i, j = np.tril_indices(k, -1)
+    keep = rng.random(len(i)) < 0.9
+    i, j = i[keep], j[keep]
+    if way == "up":
+        i, j = j, i
+    if way == "mixed":
+        p = rng.permutation(k)
+        i, j = p[i], p[j]
+        i, j = np.concatenate([i, j[:10]]), np.concatenate([j, i[:10]])
+    check(k, i.astype(np.uint32), j.astype(np.uint32))
+    if way == "down":
+        check(k, i.astype(np.uint32), j.astype(np.uint32), degree_order=True)
