@@ -286,8 +286,9 @@ def rmat22_clique_diamond_leg(gj, ctx, G, log):
         # adds 2-path endpoint counts, the 4-clique counts bits of rows): the
         # extensions are the depth-first evaluation's counters, so no rate
         out[name] = {"matches": r["matches"], "extensions": ext, "s": el,
-                     "method": ("2-path endpoint counts (closed form)" if name == "diamond" else
-                                "bit matrices of hub-side neighbours") + "; extensions = the depth-first GJ counters",
+                     "method": ("2-path counts (closed form)" if name == "diamond" else
+                                "bit matrices of hub-side neighbours, or by seed edge where a vertex has more than "
+                                "1,056 of them") + "; extensions = the depth-first GJ counters",
                      "extensions_per_s": None,
                      "matches_per_s": r["matches"] / el, "kernel_ms": r["kernel_ms"],
                      "kernel_launches": r["kernel_launches"],
@@ -329,7 +330,9 @@ def symmetry_breaking(gj, ctx, scale, log, full=False):
         r = gj.count(ctx, G, Q)
         dt = time.perf_counter() - t
         ext = sum(r["extensions"])
-        return {"matches": r["matches"], "extensions": ext, "s": dt, "extensions_per_s": ext / dt}
+        # whole cliques without inequalities propose no candidates: no rate
+        rate = ext / dt if q[0] == 3 or less else None
+        return {"matches": r["matches"], "extensions": ext, "s": dt, "extensions_per_s": rate}
 
     k5 = (5, [(i, j) for i in range(5) for j in range(i + 1, 5)], [0, 1, 2, 3, 4])
     for name, q, aut in (("triangle", tri, 6), ("4-clique", k4, 24), ("5-clique", k5, 120)):

@@ -20,11 +20,12 @@
 // are the depth-first ones: prefixes are cliques, and extensions sum the least
 // out-degree of a prefix's vertices.
 //
-// Measured (MI355X): R-MAT-20 oriented 4-clique 177 -> 7.8 ms, oriented 5-clique
-// of a 300,007-vertex R-MAT graph 20.3 -> 5.5 ms, directed R-MAT-17 4-clique
-// 90.6 -> 1.7 ms, against a wave per seed edge that probes rows in memory for
-// every a2 (clique.hip, still there for inequalities and where a vertex has
-// more than 1,056 neighbours of higher degree).  Bound by the build's probes
+// Measured (MI355X): R-MAT-20 oriented 4-clique 177 -> 7.9 ms, oriented 5-clique
+// of a 300,007-vertex R-MAT graph 20.4 -> 5.7 ms, directed R-MAT-17 4-clique
+// 90.6 -> 1.1 ms, against a wave per seed edge that probes rows in memory for
+// every a2 (clique.hip, still there for inequalities, for light graphs
+// (choose_order) and where a vertex has more than 1,056 neighbours of higher
+// degree).  Bound by the build's probes
 // and bit reads, then by the counts' LDS reads and popcounts.
 #include <algorithm>
 
@@ -160,8 +161,8 @@ __global__ void __launch_bounds__(kBlock) k_cb_classes(HubGraph g, int fits, uns
 // not built (bits[1] also where no vertex has an in-prefix).  Most members of
 // the larger v are such hubs, and a member's edges to the ones below it are
 // then bit reads, members' pairs of v only, instead of a walk of its whole
-// prefix against v's hash table (oriented R-MAT-20, 4-clique: 22.6 -> 7.8
-// ms, 5-clique at 300,007 vertices 6.9 -> 5.5 ms).
+// prefix against v's hash table (oriented R-MAT-20, 4-clique: 22.6 -> 7.9
+// ms, 5-clique at 300,007 vertices 6.9 -> 5.7 ms).
 constexpr uint32_t kCbTop = 32768;
 struct CbBits {
   const uint32_t* bits[2];
@@ -180,7 +181,7 @@ __global__ void __launch_bounds__(kBlock) k_cb_bits(HubGraph g, uint32_t top, ui
   }
 }
 
-// LDS of one v: its members' table (open addressing, at most half full, ~0 =
+// LDS of one v: its members' table (open addressing, about half full at most, ~0 =
 // free) with their positions, ids and out-degrees, the masks O and I, and the
 // matrix F: bit (i, j) is bit j & 31 of mat[(j / 32) * kStride + i], so that
 // lanes on consecutive rows read one word of each without bank conflicts (and
@@ -295,7 +296,10 @@ __device__ __forceinline__ uint32_t cb_build(CbLds<CAP, SLOTS>& s, const HubGrap
     const uint32_t cn = (uint32_t)__popcll(some);
     const uint32_t to = q ? (uint32_t)__popcll(some & lt) : cn + (uint32_t)__popcll(~some & lt);
     p = (uint32_t)__builtin_amdgcn_ds_permute(to * 4, (int)p);
-    q = (uint32_t)__builtin_amdgcn_ds_permute(to * 4, (int)(q | r << 16));  // a prefix has at most CAP entries
+    // quads in the low half: a member, as any vertex here, has at most kBigDegree
+    // entries in a prefix; r < 2 CAP in the high one
+    static_assert(kBigDegree / 4 + 1 < 1 << 16 && 2 * CAP < 1 << 16, "a row's quads and its tag in one word");
+    q = (uint32_t)__builtin_amdgcn_ds_permute(to * 4, (int)(q | r << 16));
     walk_batch<2, 16>(g.pre, p, q, cn, v, [&](uint32_t x, uint32_t tag) {
       const uint32_t j = cb_find(s, x);  // ~0 is not found
       if (j == ~0u) return;

@@ -296,7 +296,9 @@ __device__ __forceinline__ uint32_t stream_probe(const uint32_t* __restrict__ se
 // MASK: for listing; every seed edge e has a (zeroed) bit per value of its
 // proposing set, words woff[e] .. woff[e + 1] of mask, set where the value is
 // in the other set (edges of the small-set loop propose LA(x0)); seed_of maps
-// transposed entries to seed edges.  Hits are not counted.
+// transposed entries to seed edges.  Its hits are added up as without MASK but
+// mean nothing (whole words of elements go to every segment they meet);
+// k_mask_count counts the bits.
 template <bool SIGNED, bool MASK>
 __global__ void __launch_bounds__(kOwnNT) __attribute__((amdgpu_waves_per_eu(8))) k_owner_count(OwnerArgs a, const uint32_t* __restrict__ tasks,
                                                         uint32_t ntask, unsigned int* __restrict__ counter,
