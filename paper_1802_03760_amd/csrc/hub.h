@@ -1,4 +1,5 @@
-// A graph renamed so that small ids are hubs, for the whole counts that attribute a match to its least or greatest vertex (twopath.hip,
+// A graph renamed so that small ids are hubs, for the whole counts that
+// attribute a match to its least or greatest vertex (twopath.hip,
 // cliquebits.hip), and the walk over prefixes of its rows.
 #pragma once
 
@@ -11,9 +12,9 @@ namespace gj {
 // new id, row u at col[rp[u] .. rp[u + 1]); end[u] closes the prefix of ids
 // below u.  The prefixes are stored again on their own, in quads of four
 // entries padded with ~0: direction s's of u at quads [pq[s][u], pq[s][u + 1])
-// of pre, so that a walk loads 16 aligned bytes a lane
-// and an entry's value alone says whether it counts.  mq[s][u] (hub_above): the first of those quads with an id of kTpHubs
-// or above.
+// of pre, so that a walk loads 16 aligned bytes a lane and an entry's value
+// alone says whether it counts.  mq[s][u] (hub_above): the first of those quads
+// with an id of kTpHubs or above.
 struct HubGraph {
   const uint32_t* rp[2];
   const uint32_t* end[2];
@@ -58,9 +59,8 @@ __device__ __forceinline__ uint32_t lane_value(uint32_t v, int lane) {
 // side and a group that finishes one takes the batch's next; DEPTH loads are
 // in flight.  Row i < cn is lane i's: rlen & (2^LB - 1) quads from pre[rp] on,
 // with rlen >> LB as its tag.  Calls add(x, tag) for every entry and for
-// fillers (~0), so that
-// it can do without a branch per entry.  A row ends at its first quad beyond
-// lim.  Issue-bound (about 60 instructions for 256 entries): addressing is
+// fillers (~0), so that it can do without a branch per entry.  A row ends at its
+// first quad beyond lim.  Issue-bound (about 60 instructions for 256 entries): addressing is
 // per lane, since a row to a wave kept the scalar unit busy with row
 // bookkeeping, and lengths are tested per quad, not per entry.
 template <int DEPTH, int LB, class F>

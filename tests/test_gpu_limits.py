@@ -246,19 +246,20 @@ def test_cliques_without_room():
     import paper_1802_03760_amd as gj
     s, d = synth.rmat_draws(12, 16, seed=2)
     O = oracle.Graph(1 << 12, s, d)
+    want = [(q, oracle.run(O, q, threads=8)) for q in (Q.CLIQUE4, Q.CLIQUE5)]
     A = Bounded(gj)
     ctx = gj.Context(0, allocator=A)
     ctx.set_option("hash_index", 0)
     G = gj.Graph(ctx, s, d, 1 << 12)
     E = G.info()["edges"]
     A.most = 7 * E  # no 64-bit key per edge; a seed's number per edge fits
-    for q in (Q.CLIQUE4, Q.CLIQUE5):
-        same(gj.count(ctx, G, gj.Query(ctx, *q)), oracle.run(O, q, threads=8), q)
+    for q, w in want:
+        same(gj.count(ctx, G, gj.Query(ctx, *q)), w, q)
     assert A.refused
     before = A.held
     A.most = None
-    for q in (Q.CLIQUE4, Q.CLIQUE5):
-        same(gj.count(ctx, G, gj.Query(ctx, *q)), oracle.run(O, q, threads=8), q)
+    for q, w in want:
+        same(gj.count(ctx, G, gj.Query(ctx, *q)), w, q)
     assert A.held > before + 8 * E  # the refused workspace was not kept
 
 
