@@ -382,8 +382,8 @@ constexpr uint64_t kPairGain = 2, kPairWords = 2;
 
 bool Runner::by_pair(int j, uint64_t n, uint64_t W) {
   const std::vector<BindH>& b = P.bind[j];
-  if (j == 2 || collect || weighted || V.delta_atom >= 0 || !V.graph || c->arena.on || !c->run_stage || c->strategy == 1 ||
-      W < c->run_stage_min || P.above[j] || P.below[j] || b.size() != 2 || b[0].col2 >= 0 || b[1].col2 >= 0 ||
+  if (j == 2 || collect || weighted || V.delta_atom >= 0 || !V.graph || c->arena.on || !c->run_stage ||
+      c->strategy == 1 || W < c->run_stage_min || P.above[j] || P.below[j] || b.size() != 2 || b[0].col2 >= 0 || b[1].col2 >= 0 ||
       b[0].col == b[1].col)
     return false;
   const Version& v = *V.old_v;
@@ -496,9 +496,10 @@ static bool identity(const std::vector<int>& o) {
 // a million candidates.  Uniform graphs, per-candidate against listed: W = 1.6
 // m, m = 1.3e5 140 us / 165 us, m = 8.4e6 1.10 / 1.59 ms; W = 6.9 m, m = 1.3e5
 // 188 / 167 us, m = 8.4e6 2.40 / 1.53 ms; R-MAT-13 of 85,000 edges, W = 3.8e6,
-// 300 / 260 us; below kListEdges the look itself costs what is gained.  A bound on W, the 2-paths through the vertices of either side
-// of the seed edges, is known without looking at the edges (a one-way graph of
-// 1e6 edges has none: 98 us, 262 with the passes); the first pass adds W up.
+// 300 / 260 us; below kListEdges the look itself costs what is gained.  A bound
+// on W, the 2-paths through the vertices of either side of the seed edges, is
+// known without looking at the edges (a one-way graph of 1e6 edges has none: 98
+// us, 262 with the passes); the first pass adds W up.
 constexpr uint64_t kListMin = 3ull << 18, kListEdge = 3, kListEdges = 1ull << 16;
 
 static uint64_t two_paths(const Version& v, int a, int b) { return v.two[a == b ? a : 2]; }

@@ -176,9 +176,9 @@ static void row_pointers(gj_ctx* c, const uint32_t* row, uint64_t m, uint32_t n,
 }
 
 // Largest degrees of both directions, the sums over the vertices of out^2,
-// in^2 and out x in, and how many have more than kBigDegree edges: a few atomics per workgroup, into one of kDegreeSlots
-// lines (a thousand workgroups' on one address are some 25 us), which the
-// host adds up.
+// in^2 and out x in, and how many have more than kBigDegree edges: a few
+// atomics per workgroup, into one of kDegreeSlots lines (a thousand workgroups'
+// on one address are some 25 us), which the host adds up.
 constexpr int kDegreeSlots = 32;
 struct alignas(64) DegreeStats {
   uint32_t most[2];
